@@ -85,7 +85,7 @@ struct Plan {
   size_t vvec_off, vrows_off, vepc_off, vepo_off, vx_off, vq_off, vk_off, vv_off, vo_off, vh_off, va_off, vp_off;
   size_t layer_kv_elems;
   // workspace
-  size_t rows_off, counts_off, epc_off, epo_off, stats_off, x_off, q_off, o_off, r_off, act_off, xdec_off, xf_off,
+  size_t rows_off, counts_off, epc_off, epo_off, stats_off, score_off, x_off, q_off, o_off, r_off, act_off, xdec_off, xf_off,
       ssq_a_off, ssq_f_off, qraw_off, kraw_off, part_off, part_bytes,
       logits_off, rope_off, decrows_off, headrows_off, tokens_off, gate_m_off, gate_f_off, qkv3_off, bar_off,
       hpart_off, ws_bytes;
@@ -233,6 +233,7 @@ int32_t make_plan(const gvc_desc* dsc, Plan& p) {
   p.epc_off = k.take((size_t)p.L * p.B * 4);
   p.epo_off = k.take((size_t)p.L * p.B * 4);
   p.stats_off = k.take((size_t)p.B * p.N * 3 * 4);
+  p.score_off = k.take(p.stage2 ? (size_t)p.B * p.N * 4 : 0);
   p.x_off = k.take((size_t)p.Mp * p.KBx * 32 * 2);
   p.q_off = k.take((size_t)p.Mp * d.d_model * 2);
   p.o_off = k.take((size_t)p.Mp * p.KBd * 32 * 2);
@@ -1039,7 +1040,7 @@ int32_t gvc_select_static(gvc_ctx* c, const uint8_t* frame_t, const uint8_t* fra
   const float* tv = p.stage2 && c->tv_ready ? c->S<float>(p.tv_off) : nullptr;
   const float* ent = p.stage3 && c->tv_ready ? c->S<float>(p.ent_off) : nullptr;
   HIP_TRY(launch_rank_mask(stats, p.B, p.N, p.L, tau_num, tau_den, q.data(), reuse_mask, n_static, tv, p.L * p.H,
-                           p.d.task_topk, ent, p.H, p.d.n_text - 1, ent ? c->S<int>(p.lq_off) : nullptr,
+                           p.d.task_topk, c->K<float>(p.score_off), ent, p.H, p.d.n_text - 1, ent ? c->S<int>(p.lq_off) : nullptr,
                            c->stream));
   return GVC_OK;
 }
@@ -1071,7 +1072,7 @@ int32_t gvc_select_static_noalloc(const gvc_desc* desc, const uint8_t* frame_t, 
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   HIP_TRY(launch_patch_stats(frame_t, frame_prev, d.batch, d.n_views, d.img, d.patch, stats, s));
   HIP_TRY(launch_rank_mask(stats, d.batch, (int)N, d.n_layers, tau_num, tau_den, q.data(), reuse_mask, n_static,
-                           nullptr, 0, 0, nullptr, 0, 0, nullptr, s));
+                           nullptr, 0, 0, nullptr, nullptr, 0, 0, nullptr, s));
   return GVC_OK;
 }
 

@@ -18,10 +18,10 @@ hipError_t launch_zero_kv_tail(bf16* k, bf16* v, size_t n_blk, int kv_pad, int d
 hipError_t launch_patch_stats(const uint8_t* ft, const uint8_t* fp, int B, int views, int img, int patch,
                               int* stats, hipStream_t s);
 // Stage 1 (+ Stage 2 when tv != nullptr: per patch the sum over LH columns of
-// tv [B][LH][N], in order; the topk highest, ties to the lower index, are not static).
+// tv [B][LH][N], in order, into the scratch score [B][N]; the topk highest, ties to the lower index, are not static).
 hipError_t launch_rank_mask(const int* stats, int B, int N, int L, long long tau_num, long long tau_den,
                             const int* permille_host, uint8_t* mask, int* n_static, const float* tv, int LH,
-                            int topk, const float* ent, int H, int n_instr, int* q_out, hipStream_t s);
+                            int topk, float* score, const float* ent, int H, int n_instr, int* q_out, hipStream_t s);
 
 hipError_t launch_build_rows(const uint8_t* mask, const int* valid, int B, int L, int N, int P,
                              int* rows, int* counts, int* ep_counts, int* ep_offsets, hipStream_t s);

@@ -20,21 +20,32 @@ namespace gvc {
 // the library runs on holds its own copy until the process ends.
 static __device__ __align__(256) int scratch[kSelectScratchEpisodes * kSelectScratchPatches * 3];
 
-// One wave per patch: stats[(b*N + n)*3 + {0,1,2}] = dot, |u|^2, |v|^2.
+// One wave per patch: stats[(b*N + n)*3 + {0,1,2}] = dot, |u|^2, |v|^2.  A
+// frame is 150 KB, so the launch is bound by latency: each lane issues the
+// loads of kStatBatch values before it uses any (the 588 values of a 14-pixel
+// patch in one round trip; indices past the end re-read the last value).
+constexpr int kStatBatch = 10;
 __global__ __launch_bounds__(64) void k_patch_stats(const uint8_t* __restrict__ ft, const uint8_t* __restrict__ fp,
                                                     int views, int img, int patch, int* __restrict__ stats) {
   const int n = blockIdx.x, b = blockIdx.y;
   const int side = img / patch, per_view = side * side;
   const int v = n / per_view, rc = n % per_view, r = rc / side, c = rc % side;
-  const int row_bytes = patch * 3;
+  const int row_bytes = patch * 3, values = patch * row_bytes;
   const size_t frame_bytes = (size_t)views * img * img * 3;
   const size_t base = (size_t)b * frame_bytes + ((size_t)v * img * img + (size_t)r * patch * img + (size_t)c * patch) * 3;
   int dot = 0, na = 0, nb = 0;
-  for (int e = threadIdx.x; e < patch * row_bytes; e += 64) {
-    const int pr = e / row_bytes, pc = e % row_bytes;
-    const size_t off = base + (size_t)pr * img * 3 + pc;
-    const int u = ft[off], w = fp[off];
-    dot += u * w; na += u * u; nb += w * w;
+  for (int e0 = threadIdx.x; e0 < values; e0 += 64 * kStatBatch) {
+    int u[kStatBatch], w[kStatBatch];
+#pragma unroll
+    for (int i = 0; i < kStatBatch; ++i) {
+      const int e = min(e0 + 64 * i, values - 1), pr = e / row_bytes, pc = e - pr * row_bytes;
+      const size_t off = base + (size_t)pr * img * 3 + pc;
+      u[i] = ft[off];
+      w[i] = fp[off];
+    }
+#pragma unroll
+    for (int i = 0; i < kStatBatch; ++i)
+      if (e0 + 64 * i < values) { dot += u[i] * w[i]; na += u[i] * u[i]; nb += w[i] * w[i]; }
   }
   for (int o = 32; o > 0; o >>= 1) {
     dot += __shfl_down(dot, o);
@@ -47,56 +58,92 @@ __global__ __launch_bounds__(64) void k_patch_stats(const uint8_t* __restrict__ 
   }
 }
 
+// Stage 2 scores: score[b][n] = the sum of tv[b][0..LH-1][n] in that order
+// (fp32, so the order is part of the result).  A workgroup takes 16 patches:
+// all threads bring kScoreCols columns at a time to LDS with their loads in
+// flight together, and 16 threads add them in order.
+constexpr int kScorePatches = 16, kScoreCols = 512;
+__global__ __launch_bounds__(256) void k_patch_scores(const float* __restrict__ tv, int N, int LH,
+                                                      float* __restrict__ score) {
+  __shared__ float t[kScoreCols][kScorePatches];
+  const int b = blockIdx.y, n0 = blockIdx.x * kScorePatches, p = threadIdx.x % kScorePatches;
+  const float* src = tv + (size_t)b * LH * N + min(n0 + p, N - 1);
+  float sc = 0.f;
+  for (int c0 = 0; c0 < LH; c0 += kScoreCols) {
+    const int nc = min(kScoreCols, LH - c0);
+    constexpr int PER = kScoreCols * kScorePatches / 256;
+    float v[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int c = (int)threadIdx.x / kScorePatches + i * (256 / kScorePatches);
+      v[i] = src[(size_t)(c0 + min(c, nc - 1)) * N];
+    }
+    __syncthreads();   // the columns of the tile before have been added
+#pragma unroll
+    for (int i = 0; i < PER; ++i) t[(int)threadIdx.x / kScorePatches + i * (256 / kScorePatches)][p] = v[i];
+    __syncthreads();
+    if (threadIdx.x < kScorePatches)
+      for (int c = 0; c < nc; ++c) sc += t[c][p];
+  }
+  if (threadIdx.x < kScorePatches && n0 + p < N) score[(size_t)b * N + n0 + p] = sc;
+}
+
 typedef unsigned __int128 u128;
 
 struct Permille { int q[128]; };
 
-// One workgroup per episode: static flags, exact ranks, |S|, per-layer masks.
-// With tv (Stage 2), the topk patches of highest score (sum of the LH
-// columns of tv, in order; ties to the lower index) are not static.
+// Static flags, exact ranks, |S| and per-layer masks.  Workgroup (x, b) ranks
+// patches [16 x, 16 x + 16) of episode b against all N: the exact comparisons
+// (N^2 products of 128 bits) are what the launch takes, so they are spread
+// over N / 16 workgroups, one patch per wave at a time and the others over
+// its lanes (one workgroup per episode took 35 us at N = 256 and 78 us at
+// 512).  Every workgroup derives the N keys, |S| and the proportions for
+// itself from the patch statistics.
+// With score (Stage 2, [B][N]), the topk patches of highest score (ties to
+// the lower index) are not static.
 // With ent (Stage 3, [B][L][H] per-head entropy sums over n_instr tokens),
 // the per-layer proportions come from the episode's entropy: E_l = (sum over
 // heads in order) / (H n_instr), u_l = 1 - E_l, s_0 = u_0,
 // s_l = s_{l-1} + (u_l - s_{l-1}) * 0.5, q_l = floor(1000 clamp(s_l, 0, 1)),
 // in fp32 and written to q_out [B][L]; otherwise they are pm.
-__global__ __launch_bounds__(512) void k_rank_mask(const int* __restrict__ stats, int N, int L, long long tau_num,
-                                                   long long tau_den, Permille pm, uint8_t* __restrict__ mask,
-                                                   int* __restrict__ n_static, const float* __restrict__ tv, int LH,
-                                                   int topk, const float* __restrict__ ent, int H, int n_instr,
-                                                   int* __restrict__ q_out) {
+constexpr int kRankPatches = 16, kRankWaves = 4;
+__global__ __launch_bounds__(kRankWaves * 64) void k_rank_mask(
+    const int* __restrict__ stats, int N, int L, long long tau_num, long long tau_den, Permille pm,
+    uint8_t* __restrict__ mask, int* __restrict__ n_static, const float* __restrict__ score_in, int topk,
+    const float* __restrict__ ent, int H, int n_instr, int* __restrict__ q_out) {
   extern __shared__ unsigned long long sh[];   // [N] cos^2 numerator, [N] denominator (0 = not static), [N] score
   unsigned long long* knum = sh;
   unsigned long long* kden = sh + N;
   float* score = reinterpret_cast<float*>(sh + 2 * N);
-  __shared__ int s_count;
+  __shared__ int s_count, ranks[kRankPatches];
   __shared__ int qs[128];
-  const int b = blockIdx.x;
-  if (threadIdx.x == 0) {
-    s_count = 0;
-    float sl = 0.f;
-    for (int l = 0; l < L; ++l) {
-      if (ent) {
-        float e = 0.f;
-        for (int h = 0; h < H; ++h) e += ent[((size_t)b * L + l) * H + h];
-        const float u = 1.0f - e / (float)(H * n_instr);
-        sl = l == 0 ? u : sl + (u - sl) * 0.5f;
-        qs[l] = (int)floorf(1000.0f * fminf(fmaxf(sl, 0.f), 1.f));
-        q_out[(size_t)b * L + l] = qs[l];
-      } else {
-        qs[l] = pm.q[l];
-      }
+  __shared__ float us[128];
+  const int b = blockIdx.y, n0 = blockIdx.x * kRankPatches;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  if (tid == 0) s_count = 0;
+  for (int l = tid; l < L; l += kRankWaves * 64) {
+    if (ent) {
+      float e = 0.f;
+      for (int h = 0; h < H; ++h) e += ent[((size_t)b * L + l) * H + h];
+      us[l] = 1.0f - e / (float)(H * n_instr);
+    } else {
+      qs[l] = pm.q[l];
     }
   }
-  if (tv)
-    for (int n = threadIdx.x; n < N; n += blockDim.x) {
-      float sc = 0.f;
-      for (int c = 0; c < LH; ++c) sc += tv[((size_t)b * LH + c) * N + n];
-      score[n] = sc;
-    }
+  if (score_in)
+    for (int n = tid; n < N; n += kRankWaves * 64) score[n] = score_in[(size_t)b * N + n];
   __syncthreads();
+  if (ent && tid == 0) {
+    float sl = 0.f;
+    for (int l = 0; l < L; ++l) {
+      sl = l == 0 ? us[0] : sl + (us[l] - sl) * 0.5f;
+      qs[l] = (int)floorf(1000.0f * fminf(fmaxf(sl, 0.f), 1.f));
+      if (blockIdx.x == 0) q_out[(size_t)b * L + l] = qs[l];
+    }
+  }
   const unsigned long long num2 = (unsigned long long)(tau_num * tau_num);
   const unsigned long long den2 = (unsigned long long)(tau_den * tau_den);
-  for (int n = threadIdx.x; n < N; n += blockDim.x) {
+  for (int n = tid; n < N; n += kRankWaves * 64) {
     const int* s = stats + ((size_t)b * N + n) * 3;
     const long long dot = s[0], na = s[1], nb = s[2];
     unsigned long long kn = 0, kd = 0;   // kd == 0 marks "not static"
@@ -107,7 +154,7 @@ __global__ __launch_bounds__(512) void k_rank_mask(const int* __restrict__ stats
       const unsigned long long nn = (unsigned long long)na * (unsigned long long)nb;
       if ((u128)d2 * den2 > (u128)nn * num2) { kn = d2; kd = nn; }
     }
-    if (kd && tv) {   // Stage 2: a task-relevant patch is recomputed
+    if (kd && score_in) {   // Stage 2: a task-relevant patch is recomputed
       const float sn = score[n];
       int above = 0;
       for (int j = 0; j < N; ++j) above += score[j] > sn || (score[j] == sn && j < n);
@@ -118,23 +165,31 @@ __global__ __launch_bounds__(512) void k_rank_mask(const int* __restrict__ stats
   }
   __syncthreads();
   const int S = s_count;
-  for (int n = threadIdx.x; n < N; n += blockDim.x) {
-    const unsigned long long kn = knum[n], kd = kden[n];
-    int rank = 0;
-    if (kd) {
-      for (int j = 0; j < N; ++j) {
-        const unsigned long long jd = kden[j];
-        if (!jd || j == n) continue;
-        const u128 lhs = (u128)knum[j] * kd, rhs = (u128)kn * jd;   // cos_j^2 vs cos_n^2
-        rank += (lhs > rhs) || (lhs == rhs && j < n);
+  for (int i = wv; i < kRankPatches; i += kRankWaves) {
+    const int n = n0 + i;
+    int rank = -1;   // not static
+    if (n < N && kden[n]) {
+      const unsigned long long kn = knum[n], kd = kden[n];
+      rank = 0;
+      for (int j0 = 0; j0 < N; j0 += 64) {
+        const int j = j0 + lane;
+        bool before = false;
+        if (j < N && j != n && kden[j]) {
+          const u128 lhs = (u128)knum[j] * kd, rhs = (u128)kn * kden[j];   // cos_j^2 vs cos_n^2
+          before = (lhs > rhs) || (lhs == rhs && j < n);
+        }
+        rank += __popcll(__ballot(before));
       }
     }
-    for (int l = 0; l < L; ++l) {
-      const int k = (int)(((long long)qs[l] * S) / 1000);
-      mask[((size_t)b * L + l) * N + n] = (kd && rank < k) ? 1 : 0;
-    }
+    if (lane == 0) ranks[i] = rank;
   }
-  if (threadIdx.x == 0 && n_static) n_static[b] = S;
+  __syncthreads();
+  for (int e = tid; e < L * kRankPatches; e += kRankWaves * 64) {
+    const int l = e / kRankPatches, i = e % kRankPatches, n = n0 + i;
+    const int k = (int)(((long long)qs[l] * S) / 1000);
+    if (n < N) mask[((size_t)b * L + l) * N + n] = (ranks[i] >= 0 && ranks[i] < k) ? 1 : 0;
+  }
+  if (blockIdx.x == 0 && tid == 0 && n_static) n_static[b] = S;
 }
 
 // Device address of this GPU's copy of `scratch`, looked up once per device
@@ -169,13 +224,19 @@ hipError_t launch_patch_stats(const uint8_t* ft, const uint8_t* fp, int B, int v
 
 hipError_t launch_rank_mask(const int* stats, int B, int N, int L, long long tau_num, long long tau_den,
                             const int* permille_host, uint8_t* mask, int* n_static, const float* tv, int LH,
-                            int topk, const float* ent, int H, int n_instr, int* q_out, hipStream_t s) {
-  if (L > 128 || (ent && (!q_out || H < 1 || n_instr < 1))) return hipErrorInvalidValue;
+                            int topk, float* score, const float* ent, int H, int n_instr, int* q_out, hipStream_t s) {
+  if (L > 128 || (ent && (!q_out || H < 1 || n_instr < 1)) || (tv && !score)) return hipErrorInvalidValue;
   Permille pm;
   for (int l = 0; l < 128; ++l) pm.q[l] = l < L ? permille_host[l] : 0;
+  if (tv) {
+    hipLaunchKernelGGL(k_patch_scores, dim3((N + kScorePatches - 1) / kScorePatches, B), dim3(256), 0, s, tv, N, LH,
+                       score);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   const size_t shm = (size_t)N * 2 * sizeof(unsigned long long) + (size_t)N * sizeof(float);
-  hipLaunchKernelGGL(k_rank_mask, dim3(B), dim3(512), shm, s, stats, N, L, tau_num, tau_den, pm, mask, n_static, tv,
-                     LH, topk, ent, H, n_instr, q_out);
+  hipLaunchKernelGGL(k_rank_mask, dim3((N + kRankPatches - 1) / kRankPatches, B), dim3(kRankWaves * 64), shm, s, stats,
+                     N, L, tau_num, tau_den, pm, mask, n_static, tv ? score : nullptr, topk, ent, H, n_instr, q_out);
   return hipGetLastError();
 }
 
