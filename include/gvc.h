@@ -331,7 +331,9 @@ enum gvc_kernel_class {
 int32_t gvc_profile_begin(gvc_ctx* ctx, int32_t cls, int32_t max_launches);
 
 /* Stops timing, synchronizes the stream and returns the summed elapsed time
- * of the recorded launches (milliseconds) and their count.  Errors:
+ * of the recorded launches (milliseconds) and their count (the launch that
+ * runs several decode passes counts as that many, so that the quotient is the
+ * time of one GVC_K_DECODE_PASS pass).  Errors:
  * GVC_ESTATE if no profile is running, GVC_EDEVICE. */
 int32_t gvc_profile_end(gvc_ctx* ctx, double* total_ms, int32_t* launches);
 

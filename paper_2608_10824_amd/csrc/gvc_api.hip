@@ -327,7 +327,8 @@ struct gvc_ctx {
   // launch timing of one kernel class (gvc_profile_begin / _end)
   int prof_cls = -1;
   std::vector<hipEvent_t> prof_ev;
-  int prof_n = 0;
+  int prof_n = 0;         // event pairs recorded
+  int prof_units = 0;     // launches they count as (a decode launch of n passes counts n)
   std::vector<int> counts;
 
   template <class T> T* W(size_t off) const { return reinterpret_cast<T*>(w + off); }
@@ -382,13 +383,16 @@ int nt_of(const GemmArgs& a) {
 struct ProfScope {
   gvc_ctx* c;
   bool on;
-  ProfScope(gvc_ctx* ctx, int cls) : c(ctx), on(ctx->prof_cls == cls && 2 * ctx->prof_n + 1 < (int)ctx->prof_ev.size()) {
+  int units;
+  ProfScope(gvc_ctx* ctx, int cls, int n = 1)
+      : c(ctx), on(ctx->prof_cls == cls && 2 * ctx->prof_n + 1 < (int)ctx->prof_ev.size()), units(n) {
     if (on) (void)hipEventRecord(c->prof_ev[2 * c->prof_n], c->stream);
   }
   ~ProfScope() {
     if (on) {
       (void)hipEventRecord(c->prof_ev[2 * c->prof_n + 1], c->stream);
       ++c->prof_n;
+      c->prof_units += units;
     }
   }
 };
@@ -810,6 +814,7 @@ bool setup_persist(gvc_ctx* c) {
   a.kc = c->Kc(0); a.vc = c->Vc(0); a.kv_layer_elems = p.layer_kv_elems;
   a.gains = c->W<float>(p.gains_off);
   a.rope = c->K<float2>(p.rope_off);
+  a.embed = c->W<bf16>(p.embed_off);
   a.x = c->K<float>(p.xdec_off);
   a.racc = c->K<unsigned long long>(p.r_off);   // d int64 accumulators (the region holds Mp >= 16 rows of d floats)
   a.qkv = c->K<float>(p.qkv3_off);
@@ -1209,43 +1214,47 @@ int32_t gvc_decode_actions(gvc_ctx* c, int32_t* tokens_out, float* margins_out, 
                                hipMemcpyDeviceToDevice, s));
     float* xdec = c->K<float>(p.xdec_off);
     float* lg = c->K<float>(p.logits_off);
-    for (int j = 1; j < p.D; ++j) {
+    if (c->persist) {
+      // every barrier word but the abort word, which stays set until a gate reports it
+      HIP_TRY(launch_fill_u32(c->K<uint32_t>(p.bar_off), 0u, kDecodeAbortWord, s));
+      HIP_TRY(launch_fill_u32(c->K<uint32_t>(p.bar_off) + kDecodeAbortWord + 1, 0u,
+                              kDecodeBarWords - kDecodeAbortWord - 1, s));
+    }
+    // The single-launch decode runs all D - 1 passes at once when it also
+    // chooses the tokens; else one pass per launch.
+    const bool fused = c->persist && (c->dargs.flags & kDecodeHead) != 0;
+    for (int j = 1; j < p.D; j += fused ? p.D - 1 : 1) {
       const int* src = forced_tokens ? forced_tokens + (j - 1) : tok + (j - 1);
-      HIP_TRY(launch_embed_tokens(c->W<bf16>(p.embed_off), src, p.D, p.B, p.d.d_model, p.V, xdec,
-                                  c->W<float>(p.gains_off), c->K<bf16>(p.x_off), p.KBd, c->K<float>(p.ssq_a_off), s));
       const RowMap rows = c->dec_rows(j);
       const int pos = p.P + j - 1;
-      bool fused = false;   // the decode pass also ran the LM head and the token choice
       GemmArgs hd = base_args(c);
       hd.w[0] = c->packed(p.lm); hd.wblk[0] = p.lm.Nblk;
       hd.map = MAP_PLAIN; hd.n_pairs = (p.lm.Nblk + 1) / 2; hd.n_out = p.V; hd.KB = p.KBd;
       hd.x = c->K<bf16x8>(p.x_off);
       hd.e.rows = rows; hd.e.store = lg; hd.e.ld_store = p.V;
       if (c->persist) {
-        // all layers in one cooperative launch, then the final norm and the head
-        if (j == 1) {   // every barrier word but the abort word, which stays set until a gate reports it
-          HIP_TRY(launch_fill_u32(c->K<uint32_t>(p.bar_off), 0u, kDecodeAbortWord, s));
-          HIP_TRY(launch_fill_u32(c->K<uint32_t>(p.bar_off) + kDecodeAbortWord + 1, 0u,
-                                  kDecodeBarWords - kDecodeAbortWord - 1, s));
-        }
         DecodeArgs a = c->dargs;
-        fused = (a.flags & kDecodeHead) != 0;
+        a.tok_in = src;
+        a.forced = forced_tokens ? 1 : 0;
+        a.n_pass = fused ? p.D - 1 : 1;
         a.pos = pos;
         a.bar_base = (unsigned)((j - 1) * decode_grid_barriers(p.L, fused));
         a.hbar_base = (unsigned)((j - 1) * decode_head_barriers(p.L));
-        a.tok_out = tok + j;   // B = 1: token j of the episode
+        a.tok_out = tok + j;   // B = 1: tokens j, j + 1, ... of the episode
         a.margin_out = mg + j;
+        if (logits_out) { a.logits = logits_out + (size_t)j * p.V; a.logits_stride = p.V; }
         {
-          ProfScope ps(c, GVC_K_DECODE_PASS);
+          ProfScope ps(c, GVC_K_DECODE_PASS, a.n_pass);
           HIP_TRY(launch_decode_pass(a, c->persist_wg, s));
         }
         c->persist_ran = true;
-        if (!fused) {
-          ProfScope ps(c, GVC_K_NORM);
-          HIP_TRY(launch_rmsnorm(xdec, nullptr, p.B, p.d.d_model, c->W<float>(p.final_gain_off), p.d.rms_eps,
-                                 c->K<bf16>(p.x_off), p.KBd, c->big_gemm, s));
-        }
+        if (fused) break;
+        ProfScope ps(c, GVC_K_NORM);
+        HIP_TRY(launch_rmsnorm(xdec, nullptr, p.B, p.d.d_model, c->W<float>(p.final_gain_off), p.d.rms_eps,
+                               c->K<bf16>(p.x_off), p.KBd, c->big_gemm, s));
       } else {
+        HIP_TRY(launch_embed_tokens(c->W<bf16>(p.embed_off), src, p.D, p.B, p.d.d_model, p.V, xdec,
+                                    c->W<float>(p.gains_off), c->K<bf16>(p.x_off), p.KBd, c->K<float>(p.ssq_a_off), s));
         for (int l = 0; l < p.L; ++l) {
           int32_t r = run_layer_decode(c, l, rows, pos + 1, l == 0 ? 1 : p.d.d_model / 16);
           if (r) return r;
@@ -1254,11 +1263,9 @@ int32_t gvc_decode_actions(gvc_ctx* c, int32_t* tokens_out, float* margins_out, 
         hd.e.ssq_in = c->K<float>(p.ssq_a_off); hd.e.ssq_parts = p.d.d_model / 16;
         hd.e.norm_eps = p.d.rms_eps; hd.e.norm_dim = p.d.d_model;
       }
-      if (!fused) {
-        int32_t r = run_gemm(c, hd, EPI_STORE, p.B, GVC_K_DECODE_HEAD);
-        if (r) return r;
-        HIP_TRY(launch_logits_reduce(lg, p.B, p.V, p.bin_lo, full, tok, mg, p.D, j, 1, s));
-      }
+      int32_t r = run_gemm(c, hd, EPI_STORE, p.B, GVC_K_DECODE_HEAD);
+      if (r) return r;
+      HIP_TRY(launch_logits_reduce(lg, p.B, p.V, p.bin_lo, full, tok, mg, p.D, j, 1, s));
       if (logits_out)
         HIP_TRY(hipMemcpy2DAsync(logits_out + (size_t)j * p.V, (size_t)p.D * p.V * 4, lg, (size_t)p.V * 4,
                                  (size_t)p.V * 4, p.B, hipMemcpyDeviceToDevice, s));
@@ -1375,7 +1382,7 @@ int32_t gvc_profile_begin(gvc_ctx* c, int32_t cls, int32_t max_launches) {
   for (hipEvent_t e : c->prof_ev) (void)hipEventDestroy(e);
   c->prof_ev.assign((size_t)2 * max_launches, nullptr);
   for (auto& e : c->prof_ev) HIP_TRY(hipEventCreate(&e));
-  c->prof_n = 0;
+  c->prof_n = c->prof_units = 0;
   c->prof_cls = cls;
   return GVC_OK;
 }
@@ -1391,11 +1398,11 @@ int32_t gvc_profile_end(gvc_ctx* c, double* total_ms, int32_t* launches) {
     tot += ms;
   }
   if (total_ms) *total_ms = tot;
-  if (launches) *launches = c->prof_n;
+  if (launches) *launches = c->prof_units;
   for (hipEvent_t e : c->prof_ev) (void)hipEventDestroy(e);
   c->prof_ev.clear();
   c->prof_cls = -1;
-  c->prof_n = 0;
+  c->prof_n = c->prof_units = 0;
   return GVC_OK;
 }
 

@@ -30,6 +30,10 @@ struct DecodeArgs {
   size_t kv_layer_elems;
   const float* gains;          // [L][2][d]: attention norm, FFN norm
   const float2* rope;          // [kv_pad][head_dim/2]
+  const bf16* embed;           // [V][d] token embedding table: a pass starts from its token's row
+  const int* tok_in;           // token of the first pass; with `forced`, of pass p at tok_in[p]
+  int forced;                  // 1: every pass takes its token from tok_in, 0: from the pass before
+  int n_pass;                  // passes of this launch, at positions pos, pos + 1, ... (1 without kDecodeHead)
   float* x;                    // [d] layer input / output (in place)
   unsigned long long* racc;    // [d] sum of the heads' attention-output contributions, int64 in 2^-32 units
   float* qkv;                  // [3d] q, k, v before RoPE
@@ -45,10 +49,11 @@ struct DecodeArgs {
   // this pass (Eq. 1) after the last layer
   const bf16x8* wlm;           // packed LM head, nlm blocks of KBd fragments
   const float* final_gain;     // [d]
-  float* logits;               // [V] this pass's logits
+  float* logits;               // [V] logits of pass p at logits + p * logits_stride
+  size_t logits_stride;
   float* head_part;            // [gridDim <= kDecodeMaxGrid][8] per workgroup: max, sum, v1, i1, v2, i2
-  int* tok_out;                // the token of this pass (one int)
-  float* margin_out;           // its margin (one float)
+  int* tok_out;                // the tokens of the passes (one int each)
+  float* margin_out;           // their margins (one float each)
   int nlm, V, bin_lo, full_vocab;
 };
 constexpr int kDecodeNtWeights = 1;   // weight loads marked non-temporal
