@@ -824,16 +824,12 @@ bool setup_persist(gvc_ctx* c) {
   a.L = p.L; a.d = d; a.F = F; a.H = p.H; a.head_dim = p.dh; a.KBd = p.KBd; a.KBf = p.KBf; a.kv_pad = p.kv_pad;
   a.act_bytes = act;
   a.eps = p.d.rms_eps;
-  // Weights are read once per pass: marked non-temporal they stop evicting
-  // the activations, barrier words and key/value lines from L2 (7B: 2.93
-  // instead of 3.09 ms per pass; warming the keys and values adds 1%).
-  // GVC_DECODE_FLAGS overrides the flags (measurement).
-  // The LM head and the token choice join the pass when its blocks fit
-  // kDecodeMaxSeg per workgroup.
+  // The LM head and the token choice join the launch when its blocks fit
+  // kDecodeMaxSeg per workgroup.  GVC_DECODE_FLAGS without bit 4 keeps them
+  // out (testing).
   const bool head = ceil_div(p.lm.Nblk, G) <= kDecodeMaxSeg;
-  a.flags = kDecodeNtWeights | kDecodeWarmKv | (head ? kDecodeHead : 0);
-  if (const char* e = getenv("GVC_DECODE_FLAGS"))
-    a.flags = atoi(e) & (kDecodeNtWeights | kDecodeWarmKv | (head ? kDecodeHead : 0));
+  a.flags = head ? kDecodeHead : 0;
+  if (const char* e = getenv("GVC_DECODE_FLAGS")) a.flags &= atoi(e);
   a.wlm = c->packed(p.lm); a.nlm = p.lm.Nblk;
   a.final_gain = c->W<float>(p.final_gain_off);
   a.logits = c->K<float>(p.logits_off);

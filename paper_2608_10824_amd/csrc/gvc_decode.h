@@ -7,6 +7,7 @@ namespace gvc {
 // ------------------------------------------------------------------ persistent decode pass
 // One single-token pass over all layers for one episode (k_decode.hip).
 constexpr int kDecodeMaxSeg = 8;       // weight blocks per workgroup per step
+constexpr int kDecodeMaxSegs = 5 * kDecodeMaxSeg;   // of a wave in one layer (4 steps) and the LM head
 constexpr int kDecodeAbortWord = 512;  // barrier words: abort flag
 constexpr int kDecodeXccWord = 544;    // barrier words: set when a workgroup is not on XCD blockIdx % 8
 constexpr int kDecodePoisonWord = 576; // barrier words: set when a head contribution was not finite
@@ -44,7 +45,7 @@ struct DecodeArgs {
   long long timeout_ticks;     // barrier wait limit in wall-clock ticks (100 MHz)
   int L, d, F, H, head_dim, KBd, KBf, kv_pad, pos, act_bytes;
   float eps;
-  int flags;                   // kDecodeNtWeights | kDecodeWarmKv | kDecodeHead
+  int flags;                   // kDecodeHead or 0
   // with kDecodeHead: final norm, LM head and the greedy token and margin of
   // this pass (Eq. 1) after the last layer
   const bf16x8* wlm;           // packed LM head, nlm blocks of KBd fragments
@@ -56,8 +57,6 @@ struct DecodeArgs {
   float* margin_out;           // their margins (one float each)
   int nlm, V, bin_lo, full_vocab;
 };
-constexpr int kDecodeNtWeights = 1;   // weight loads marked non-temporal
-constexpr int kDecodeWarmKv = 2;      // step 1 pulls the head's cached keys and values into L2
 constexpr int kDecodeHead = 4;        // the pass ends with the LM head and the token choice
 
 }  // namespace gvc

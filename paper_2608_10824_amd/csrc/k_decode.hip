@@ -82,6 +82,12 @@ constexpr int kScoreOffset = 256;              // attention scores follow the he
 // ring fragments consumed per round in each step (see run_step)
 constexpr std::integral_constant<int, 1> kUnQkv{}, kUnGu{}, kUnDown{};
 constexpr std::integral_constant<int, 2> kUnO{};
+constexpr std::integral_constant<int, 0> kNone{};
+// Key and value loads a compute thread keeps in flight through step 1 (16
+// bytes each): with head dimension 128 they hold the first 288 keys and values
+// of the head over the workgroup, 576 with 64; longer caches load the rest
+// during the attention.
+constexpr int kKvLoads = 9;
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
@@ -214,11 +220,11 @@ __device__ bool head_sync(const DecodeArgs& a, int h, unsigned n, unsigned k) {
   return __builtin_amdgcn_readfirstlane(ok) != 0;
 }
 
-// Staging of a step's input into LDS by the compute waves (threads 0..511;
-// the synchronising wave only joins the block barrier).  Their coherent
-// loads queue behind the ring in the memory counter, but the ring's loads
-// have landed during the grid barrier, and one round trip with 512 threads
-// beats several with one wave.
+// Staging of a step's input into LDS by the compute waves (threads 0..511).
+// Their coherent loads queue behind the ring in the memory counter, but the
+// ring's loads have landed during the grid barrier, and one round trip with
+// 512 threads beats several with one wave.  stage_norm holds one block
+// barrier, which the synchronising wave joins.
 //
 // act[0..n) = bf16(src * gain / rms(src)), src fp32 [n], n % 4 == 0,
 // n <= NCH * 4 * 512; act[n..npad) = 0.  With RES, src is the residual
@@ -228,10 +234,9 @@ template <bool RES, int NCH>
 __device__ __forceinline__ void stage_norm(rsrc_t src, rsrc_t acc, const unsigned* bar, const float* __restrict__ gain,
                                            int n, int npad, float eps, bf16* act, float* wred) {
   const int tid = threadIdx.x;
-  const bool cw = tid < kWaves * 64;
   float4 y[NCH];
   float ss = 0.f;
-  if (cw) {
+  {
     // every load is issued (indices past the end re-read the last chunk, in
     // bounds) before any is used: one memory round trip, not one per chunk
     // (batches of two chunks with RES: 64-bit accumulators take registers)
@@ -270,11 +275,11 @@ __device__ __forceinline__ void stage_norm(rsrc_t src, rsrc_t acc, const unsigne
         y[i] = float4{v[i].x * g[i].x, v[i].y * g[i].y, v[i].z * g[i].z, v[i].w * g[i].w};
       }
     }
-ss = wave_sum(ss);
+    ss = wave_sum(ss);
     if ((tid & 63) == 0) wred[tid >> 6] = ss;
   }
   block_sync();
-  if (cw) {
+  {
     float tot = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) tot += wred[w];
@@ -292,7 +297,6 @@ ss = wave_sum(ss);
 // act[0..n) = src bf16 [n] (n % 8 == 0, n <= 8 * 2048), act[n..npad) = 0.
 __device__ __forceinline__ void stage_copy(rsrc_t src, int n, int npad, bf16* act) {
   const int tid = threadIdx.x;
-  if (tid >= kWaves * 64) return;
   u32x4 v[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) v[i] = ld_b128(src, min(tid + i * kWaves * 64, n / 8 - 1) * 16);   // all loads first
@@ -313,84 +317,115 @@ __device__ __forceinline__ float sum_partials(const float* red, int s, int t) {
   return v;
 }
 
+// Lane layout of the attention over one head's cache.  Score phase: DH / 8
+// lanes share a key (8 dims each), KPI keys per round.  Value phase: CG chunk
+// groups per dim, a chunk being 8 keys of one dim.
+template <int DH>
+struct AttnLanes {
+  static constexpr int NT = kWaves * 64, LPK = DH / 8, KPI = NT / LPK, U = kKvLoads, CG = NT / DH, UV = kKvLoads;
+  int sub, kg, koff, dim, cg, voff, last_cached, nchunk;
+  __device__ __forceinline__ AttnLanes(int pos, int kv_pad) {
+    const int tid = threadIdx.x;
+    sub = tid % LPK; kg = tid / LPK; koff = sub * 16;
+    dim = tid / CG; cg = tid % CG; voff = dim * kv_pad * 2;
+    last_cached = max(pos - 1, 0);
+    nchunk = (pos + 8) / 8;
+  }
+};
+
+// A compute thread's first kKvLoads key and value loads (exactly as many:
+// run_step counts them; indices past the cache re-read its last ones).
+template <int DH>
+__device__ __forceinline__ void attn_load(int h, int pos, int kv_pad, bf16* lkc, bf16* lvc, u16x8 (&kv)[kKvLoads],
+                                          u16x8 (&vv)[kKvLoads]) {
+  using A = AttnLanes<DH>;
+  const A t(pos, kv_pad);
+  const rsrc_t r_k = rsrc(lkc + (size_t)h * kv_pad * DH, (size_t)kv_pad * DH * 2);
+  const rsrc_t r_v = rsrc(lvc + (size_t)h * DH * kv_pad, (size_t)kv_pad * DH * 2);
+#pragma unroll
+  for (int u = 0; u < A::U; ++u) kv[u] = ld_plain_b128(r_k, t.koff + min(u * A::KPI + t.kg, t.last_cached) * DH * 2);
+#pragma unroll
+  for (int u = 0; u < A::UV; ++u) vv[u] = ld_plain_b128(r_v, t.voff + min(t.cg + A::CG * u, t.nchunk - 1) * 16);
+}
+
 // Attention of head h for the single token at position pos, computed by each
 // of the head's workgroups in full (they share the head's cache lines in
-// one L2); the output (DH values, bf16) goes to oact in LDS.  The compute
-// waves issue their first loads of the cached keys before the first block
-// barrier; meanwhile the synchronising wave applies RoPE to the new q and k
-// and, when `append`, writes the new key and value into the caches (for
-// later passes).  Position pos itself is read from LDS.  A key (value)
-// register is reloaded with the next batch's key (value) as soon as it has
-// been used, and the first values are loaded right after the scores, so the
-// load round trips overlap the arithmetic and the block barriers.
+// one L2); the output (DH values, bf16) goes to oact in LDS.
+//
+// The synchronising wave's part: RoPE of the new q and k, and, when `append`,
+// the new key and value into the caches (for later passes).  Position pos
+// itself is read from LDS.  Joins the four block barriers of attn_compute.
 template <int DH>
-__device__ __forceinline__ void attn_head(int h, int pos, int d, int kv_pad, bool append, bool xl, bf16* lkc,
-                                          bf16* lvc, const float2* rp, rsrc_t r_qkv, float* qs, float* kn, float* vn,
-                                          float* wred, float* sc, bf16* oact) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool syncw = wv == kWaves;
+__device__ __forceinline__ void attn_sync(int h, int pos, int d, int kv_pad, bool append, bool xl, bf16* lkc, bf16* lvc,
+                                          const float2* rp, rsrc_t r_qkv, float* qs, float* kn, float* vn) {
+  const int lane = threadIdx.x & 63;
   constexpr int half = DH / 2;
-  constexpr int NT = kWaves * 64;
-  constexpr int LPK = DH / 8, KPI = NT / LPK, U = 5;   // score phase: 8 dims per lane, U key rounds per batch
-  constexpr int CG = NT / DH, UV = 5;                  // value phase: CG chunk groups per dim, UV chunks per batch
-  const int n_keys = pos + 1, nchunk = (n_keys + 7) / 8;
-  const int last_cached = max(pos - 1, 0);
-  bf16* kbase = lkc + (size_t)h * kv_pad * DH;
-  bf16* vbase = lvc + (size_t)h * DH * kv_pad;
-  const rsrc_t r_k = rsrc(kbase, (size_t)kv_pad * DH * 2);
-  const rsrc_t r_v = rsrc(vbase, (size_t)kv_pad * DH * 2);
-  const int sub = tid % LPK, kg = tid / LPK;           // score phase: key slice, key of the round
-  const int koff = sub * 16;
-  const int dim = tid / CG, cg = tid % CG;             // value phase: dim, chunk group
-  const int voff = dim * kv_pad * 2;
-  u16x8 kv[U], vv[UV];
-  if (!syncw) {
+  // every load first (one round trip), then RoPE and the appends
+  constexpr int NH = (half + 63) / 64, NV = (DH + 63) / 64;
+  float q0[NH], q1[NH], k0[NH], k1[NH], vr[NV];
 #pragma unroll
-    for (int u = 0; u < U; ++u) kv[u] = ld_plain_b128(r_k, koff + min(u * KPI + kg, last_cached) * DH * 2);
-  } else {
-    // every load first (one round trip), then RoPE and the appends
-    constexpr int NH = (half + 63) / 64, NV = (DH + 63) / 64;
-    float q0[NH], q1[NH], k0[NH], k1[NH], vr[NV];
+  for (int n = 0; n < NH; ++n) {
+    const int qo = h * DH + min(lane + 64 * n, half - 1);
+    q0[n] = ld_f32_x(r_qkv, qo * 4, xl);
+    q1[n] = ld_f32_x(r_qkv, (qo + half) * 4, xl);
+    k0[n] = ld_f32_x(r_qkv, (d + qo) * 4, xl);
+    k1[n] = ld_f32_x(r_qkv, (d + qo + half) * 4, xl);
+  }
 #pragma unroll
-    for (int n = 0; n < NH; ++n) {
-      const int qo = h * DH + min(lane + 64 * n, half - 1);
-      q0[n] = ld_f32_x(r_qkv, qo * 4, xl);
-      q1[n] = ld_f32_x(r_qkv, (qo + half) * 4, xl);
-      k0[n] = ld_f32_x(r_qkv, (d + qo) * 4, xl);
-      k1[n] = ld_f32_x(r_qkv, (d + qo + half) * 4, xl);
-    }
+  for (int n = 0; n < NV; ++n) vr[n] = ld_f32_x(r_qkv, (2 * d + h * DH + min(lane + 64 * n, DH - 1)) * 4, xl);
+  const rsrc_t r_k = rsrc(lkc + (size_t)h * kv_pad * DH, (size_t)kv_pad * DH * 2);
+  const rsrc_t r_v = rsrc(lvc + (size_t)h * DH * kv_pad, (size_t)kv_pad * DH * 2);
 #pragma unroll
-    for (int n = 0; n < NV; ++n) vr[n] = ld_f32_x(r_qkv, (2 * d + h * DH + min(lane + 64 * n, DH - 1)) * 4, xl);
-#pragma unroll
-    for (int n = 0; n < NH; ++n) {
-      const int i = lane + 64 * n;
-      if (i < half) {
-        const float2 cs = rp[i];
-        qs[i] = q0[n] * cs.x - q1[n] * cs.y;
-        qs[i + half] = q1[n] * cs.x + q0[n] * cs.y;
-        const bf16 ka = f2bf(k0[n] * cs.x - k1[n] * cs.y), kb = f2bf(k1[n] * cs.x + k0[n] * cs.y);
-        kn[i] = bf2f(ka);
-        kn[i + half] = bf2f(kb);
-        if (append) {
-          st_b16(r_k, (pos * DH + i) * 2, ka);
-          st_b16(r_k, (pos * DH + i + half) * 2, kb);
-        }
-      }
-    }
-#pragma unroll
-    for (int n = 0; n < NV; ++n) {
-      const int i = lane + 64 * n;
-      if (i < DH) {
-        const bf16 v = f2bf(vr[n]);
-        vn[i] = bf2f(v);
-        if (append) st_b16(r_v, (i * kv_pad + pos) * 2, v);
+  for (int n = 0; n < NH; ++n) {
+    const int i = lane + 64 * n;
+    if (i < half) {
+      const float2 cs = rp[i];
+      qs[i] = q0[n] * cs.x - q1[n] * cs.y;
+      qs[i + half] = q1[n] * cs.x + q0[n] * cs.y;
+      const bf16 ka = f2bf(k0[n] * cs.x - k1[n] * cs.y), kb = f2bf(k1[n] * cs.x + k0[n] * cs.y);
+      kn[i] = bf2f(ka);
+      kn[i + half] = bf2f(kb);
+      if (append) {
+        st_b16(r_k, (pos * DH + i) * 2, ka);
+        st_b16(r_k, (pos * DH + i + half) * 2, kb);
       }
     }
   }
+#pragma unroll
+  for (int n = 0; n < NV; ++n) {
+    const int i = lane + 64 * n;
+    if (i < DH) {
+      const bf16 v = f2bf(vr[n]);
+      vn[i] = bf2f(v);
+      if (append) st_b16(r_v, (i * kv_pad + pos) * 2, v);
+    }
+  }
+  block_sync();
+  block_sync();
+  block_sync();
+  block_sync();
+}
+
+// The compute waves' part.  kv and vv hold the first keys and values
+// (attn_load, issued before step 1's weight loop), so a cache of up to
+// KPI * U keys is not waited for here; for longer ones a key (value) register
+// is reloaded with the next batch's as soon as it has been used.
+template <int DH>
+__device__ __forceinline__ void attn_compute(int h, int pos, int kv_pad, const bf16* lkc, const bf16* lvc,
+                                             const float* qs, const float* kn, const float* vn, float* wred, float* sc,
+                                             bf16* oact, u16x8 (&kv)[kKvLoads], u16x8 (&vv)[kKvLoads]) {
+  using A = AttnLanes<DH>;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int NT = A::NT, LPK = A::LPK, KPI = A::KPI, U = A::U, CG = A::CG, UV = A::UV;
+  const int n_keys = pos + 1;
+  const A t(pos, kv_pad);
+  const int nchunk = t.nchunk, sub = t.sub, kg = t.kg, dim = t.dim, cg = t.cg;
+  const rsrc_t r_k = rsrc(lkc + (size_t)h * kv_pad * DH, (size_t)kv_pad * DH * 2);
+  const rsrc_t r_v = rsrc(lvc + (size_t)h * DH * kv_pad, (size_t)kv_pad * DH * 2);
   block_sync();
   // scores q . k_j / sqrt(d_h), j <= pos
   float mx = -INFINITY;
-  if (!syncw) {
+  {
     float qv[8], kv_new[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) { qv[i] = qs[sub * 8 + i]; kv_new[i] = kn[sub * 8 + i]; }
@@ -399,6 +434,7 @@ __device__ __forceinline__ void attn_head(int h, int pos, int d, int kv_pad, boo
       const bool more = j0 + KPI * U < n_keys;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
+        if (j0 + u * KPI >= n_keys) break;
         const int j = j0 + u * KPI + kg;
         float s = 0.f;
         if (j == pos) {
@@ -409,8 +445,8 @@ __device__ __forceinline__ void attn_head(int h, int pos, int d, int kv_pad, boo
           for (int i = 0; i < 8; ++i) s += qv[i] * bf2f(kv[u][i]);
         }
         // the slot takes the next batch's key at once
-        if (more) kv[u] = ld_plain_b128(r_k, koff + min(j + KPI * U, last_cached) * DH * 2);
-s = group_sum<LPK>(s);
+        if (more) kv[u] = ld_plain_b128(r_k, t.koff + min(j + KPI * U, t.last_cached) * DH * 2);
+        s = group_sum<LPK>(s);
         s *= scale;
         if (j < n_keys) {
           if (sub == 0) sc[j] = s;
@@ -418,15 +454,12 @@ s = group_sum<LPK>(s);
         }
       }
     }
-    // the first values are in flight through the softmax
-#pragma unroll
-    for (int u = 0; u < UV; ++u) vv[u] = ld_plain_b128(r_v, voff + min(cg + CG * u, nchunk - 1) * 16);
     mx = wave_max(mx);
     if (lane == 0) wred[wv] = mx;
   }
   block_sync();
-  float sm = 0.f;
-  if (!syncw) {
+  {
+    float sm = 0.f;
     mx = wred[0];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) mx = fmaxf(mx, wred[w]);
@@ -435,15 +468,12 @@ s = group_sum<LPK>(s);
       sc[j] = p;
       sm += p;
     }
-    sm = wave_sum(sm);
-  }
-  block_sync();
-  if (!syncw) {
-    if (lane == 0) wred[8 + wv] = sm;
     for (int j = n_keys + tid; j < nchunk * 8; j += NT) sc[j] = 0.f;   // pad the last 8-key chunk
+    sm = wave_sum(sm);
+    if (lane == 0) wred[8 + wv] = sm;
   }
   block_sync();
-  if (!syncw) {
+  {
     float tot = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) tot += wred[8 + w];
@@ -460,10 +490,10 @@ s = group_sum<LPK>(s);
 #pragma unroll
           for (int e = 0; e < 8; ++e) acc += pp[e] * (c * 8 + e == pos ? vnew : bf2f(vv[u][e]));
         }
-        if (more) vv[u] = ld_plain_b128(r_v, voff + min(c + CG * UV, nchunk - 1) * 16);
+        if (more) vv[u] = ld_plain_b128(r_v, t.voff + min(c + CG * UV, nchunk - 1) * 16);
       }
     }
-acc = group_sum<CG>(acc);
+    acc = group_sum<CG>(acc);
     if (cg == 0) oact[dim] = f2bf(acc / tot);
   }
   block_sync();
@@ -482,7 +512,7 @@ __global__ __launch_bounds__(kThreads) void k_decode_pass(const DecodeArgs a) {
   __shared__ float qs[DH], kn[DH], vn[DH], wred[16];
   __shared__ float2 rp[DH / 2];
   __shared__ int s_ok;
-  __shared__ u32x4 sink[64];   // destination of the cache-warming loads
+  __shared__ int2 segtab[kWaves * kDecodeMaxSegs];
 
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool syncw = wv == kWaves;
@@ -507,348 +537,372 @@ __global__ __launch_bounds__(kThreads) void k_decode_pass(const DecodeArgs a) {
   const int ob0w = w8 * nsb / kWaves, nseg_o = syncw ? 0 : (w8 + 1) * nsb / kWaves - ob0w;
   const int gp0 = gi * nf / G, nseg2 = 2 * ((gi + 1) * nf / G - gp0);     // gate, up, gate, up, ...
   const int db0 = gi * nq / G, nseg3 = (gi + 1) * nq / G - db0;           // down blocks (k split)
-  const int nsegs = nseg0 + nseg_o + nseg2 + nseg3;   // segments of one layer, in stream order
   // step 5 (kDecodeHead): LM head blocks [hb0, hb0 + nh) (k split), streamed
   // as one more "layer" after the last one
   const bool head = (a.flags & kDecodeHead) != 0;
   const int hb0 = head ? gi * a.nlm / G : 0, nh = head ? (gi + 1) * a.nlm / G - hb0 : 0;
-  const int Lend = a.L + (head ? 1 : 0);
 
   const rsrc_t r_x = rsrc(a.x, (size_t)d * 4), r_acc = rsrc(a.racc, (size_t)d * 8);
-  const rsrc_t r_qkv = rsrc(a.qkv, (size_t)3 * d * 4);
   const rsrc_t r_act = rsrc(a.act, (size_t)F * 2);
 
-  // First fragment of segment sg of layer 0 for this wave (offset from wq,
-  // in bf16x8 units) and its length.  Everything here is wave-uniform and
-  // kept in locals: selects between kernel-argument fields would be turned
-  // into indexed private memory.
-  const bf16x8* const wq = a.wq;
-  const long long off_o = a.wo - a.wq, off_g = a.wg - a.wq, off_d = a.wd - a.wq;
-  const bf16x8* const lm0 = head ? a.wlm + ((long long)hb0 * a.KBd + k0d) * 64 : wq;   // head block hb0, k step k0d
-  const long long qkv_stride = (long long)a.qkv_stride, gu_stride = (long long)a.gu_stride;
-  const long long KBd = a.KBd, KBf = a.KBf;
-  auto seg_off = [=](int sg) -> long long {
-    if (sg < nseg0) {
-      const int m = sg / nbm, rb = qb0 + sg - m * nbm;
-      return m * qkv_stride + (rb * KBd + k0d) * 64;
+  // The two roles run the same sequence of block barriers, each in a loop of
+  // its own: one body for both kept the other role's values live and spilled
+  // 290 scalar registers into the weight loop.
+  if (!syncw) {
+    // Weight stream of a compute wave: its segments of one layer in stream
+    // order, then its LM head blocks, as a table in LDS of (offset from wq in
+    // 256-byte units, fragments), empty segments left out.  Layer l's copy of a
+    // layer segment is l * layer_stride further.  (Computed from the kernel's
+    // arguments per segment instead, the 64-bit strides and block ranges cost
+    // 290 spilled scalar registers, read back inside the weight loop.)
+    constexpr int kUnit = 16;   // bf16x8 per table unit
+    int2* const mytab = segtab + wv * kDecodeMaxSegs;
+    int n_ls = 0, n_hs = 0;     // layer segments, head blocks of this wave
+    {
+      const long long KBd = a.KBd, KBf = a.KBf;
+      int sg = lane, len = 0;
+      long long off = 0;
+      if (sg < nseg0) {
+        const int m = sg / nbm, rb = qb0 + sg - m * nbm;
+        off = m * (long long)a.qkv_stride + (rb * KBd + k0d) * 64;
+        len = nkd;
+      } else if ((sg -= nseg0) < nseg_o) {
+        off = (a.wo - a.wq) + ((sb0 + ob0w + sg) * KBd + ah * KH) * 64;
+        len = KH;
+      } else if ((sg -= nseg_o) < nseg2) {
+        off = (a.wg - a.wq) + (sg & 1) * (long long)a.gu_stride + ((gp0 + (sg >> 1)) * KBd + k0d) * 64;
+        len = nkd;
+      } else if ((sg -= nseg2) < nseg3) {
+        off = (a.wd - a.wq) + ((db0 + sg) * KBf + k0f) * 64;
+        len = nkf;
+      }
+      const unsigned long long ls = __ballot(len > 0), below = (1ull << lane) - 1;
+      n_ls = __popcll(ls);
+      if (len > 0) mytab[__popcll(ls & below)] = int2{(int)(off / kUnit), len};
+      n_hs = nkd > 0 ? nh : 0;
+      if (lane < n_hs) mytab[n_ls + lane] = int2{(int)((a.wlm - a.wq + ((hb0 + lane) * KBd + k0d) * 64) / kUnit), nkd};
     }
-    sg -= nseg0;
-    if (sg < nseg_o) return off_o + ((sb0 + ob0w + sg) * KBd + ah * KH) * 64;
-    sg -= nseg_o;
-    if (sg < nseg2) return off_g + (sg & 1) * gu_stride + ((gp0 + (sg >> 1)) * KBd + k0d) * 64;
-    sg -= nseg2;
-    return off_d + ((db0 + sg) * KBf + k0f) * 64;
-  };
-  // (arithmetic rather than a select chain, which becomes an indexed table in private memory)
-  auto seg_len = [=](int sg) -> int {
-    const int in_o = (sg >= nseg0) & (sg < nseg0 + nseg_o), in_d = sg >= nseg0 + nseg_o + nseg2;
-    return nkd + in_o * (KH - nkd) + in_d * (nkf - nkd);
-  };
 
-  // Producer state of a compute wave: pass, layer, segment, fragments left in
-  // the segment, next fragment (layer 0 address plus layer * layer_stride).
-  int p_pass = 0, p_l = 0, p_sg = 0, p_left = 0;
-  const bf16x8* p_ptr = nullptr;
-  const bf16x8* last = nullptr;
-  int slot = 0;
-  u32x4* myring = ring + wv * kRing * 64;
-  const bool nt_w = (a.flags & kDecodeNtWeights) != 0;
-  const bool streams = !syncw && (nseg0 + nseg2 + nh) * nkd + nseg_o * KH + nseg3 * nkf > 0;
-  const long long layer_stride = (long long)a.layer_stride;
-  // moves to the next non-empty segment at or after (p_pass, p_l, p_sg);
-  // layer a.L (with the head step) holds the LM head blocks
-  auto settle = [&]() {
-    while (true) {
-      if (p_l >= Lend) {
-        if (p_pass + 1 >= a.n_pass) return;
-        ++p_pass;
-        p_l = 0;
-      }
-      const bool hl = p_l == a.L;
-      const int len = hl ? (p_sg < nh ? nkd : 0) : (p_sg < nsegs ? seg_len(p_sg) : 0);   // a layer may have no segments
-      if (len > 0) {
-        p_ptr = hl ? lm0 + p_sg * KBd * 64 : wq + seg_off(p_sg) + p_l * layer_stride;
-        p_left = len;
-        return;
-      }
-      if (++p_sg >= (hl ? nh : nsegs)) { p_sg = 0; ++p_l; }
-    }
-  };
-  auto issue = [&](int sl) {
-    const bf16x8* ptr = last;   // past the end: re-read the final fragment (in bounds, cached)
-    if (p_l < Lend) {
-      ptr = p_ptr;
-      last = ptr;
-      p_ptr += 64;
-      if (--p_left == 0) {
-        if (++p_sg >= (p_l == a.L ? nh : nsegs)) { p_sg = 0; ++p_l; }
-        settle();
-      }
-    }
-    if (nt_w)
-      __builtin_amdgcn_global_load_lds(GP(ptr + lane), LP(myring + sl * 64), 16, 0, 2);
-    else
-      __builtin_amdgcn_global_load_lds(GP(ptr + lane), LP(myring + sl * 64), 16, 0, 0);
-  };
-  if (streams) {
-    settle();
-#pragma unroll 1
-    for (int f = 0; f < kRing; ++f) issue(f);
-  }
-
-  // Compute waves: nseg blocks of nk k steps each over the staged activation
-  // (k steps k0.. of act); partial sums to red[wave][block].  Fragments are
-  // consumed UN at a time: the UN oldest ring loads have landed, their LDS
-  // reads overlap, then their slots are refilled.  A step whose fragments
-  // are already in the ring (the output projection after the attention) is
-  // bound by this loop, not by HBM.
-  auto run_step = [&](auto un, int nseg, int nk, int k0) {
-    constexpr int UN = decltype(un)::value;
-    const bf16* abase = act + (lane >> 4) * 8;
-    const bool row0 = (lane & 15) == 0;
-    for (int s = 0; s < nseg; ++s) {
-      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-      int j = 0;
-      if constexpr (UN > 1) {
-        for (; j + UN <= nk; j += UN) {
-          wait_vm<kRing - UN>();
-          u32x4 wf[UN], xf[UN];
-#pragma unroll
-          for (int u = 0; u < UN; ++u) {
-            const int sl = slot + u < kRing ? slot + u : slot + u - kRing;
-            wf[u] = myring[sl * 64 + lane];
-            xf[u] = *(const u32x4*)(abase + (k0 + j + u) * 32);
-            if (!row0) xf[u] = u32x4{0u, 0u, 0u, 0u};
-          }
-#pragma unroll
-          for (int u = 0; u < UN; ++u)
-            acc = mfma16(__builtin_bit_cast(bf16x8, xf[u]), __builtin_bit_cast(bf16x8, wf[u]), acc);
-          wait_lgkm0();
-#pragma unroll
-          for (int u = 0; u < UN; ++u) {
-            issue(slot);
-            slot = slot + 1 == kRing ? 0 : slot + 1;
-          }
+    // Producer state: pass, layer (a.L: the LM head), table entry, fragments
+    // left in it, the next fragment, the layer's base.
+    int p_pass = 0, p_l = 0, p_i = 0, p_left = 0;
+    const bf16x8* p_base = a.wq;
+    const bf16x8* p_ptr = a.wq;   // past the end: stays on the final fragment (in bounds, cached)
+    int slot = 0;
+    u32x4* myring = ring + wv * kRing * 64;
+    const bool streams = n_ls + n_hs > 0;
+    // moves to the next table entry; at the end of the last pass p_left stays 0
+    auto settle = [&]() {
+      while (p_i >= (p_l < a.L ? n_ls : n_ls + n_hs)) {   // the layer's entries are used up
+        if (++p_l > a.L || (p_l == a.L && n_hs == 0)) {
+          if (p_pass + 1 >= a.n_pass) return;
+          ++p_pass;
+          p_l = 0;
         }
+        p_i = p_l < a.L ? 0 : n_ls;
+        p_base = a.wq + (p_l < a.L ? p_l * (long long)a.layer_stride : 0ll);
+        if (n_ls == 0 && p_l < a.L) { p_l = a.L; p_i = 0; p_base = a.wq; }   // head blocks only
       }
-      for (; j < nk; ++j) {
-        wait_vm<kRing - 1>();
-        const u32x4 wf = myring[slot * 64 + lane];
-        u32x4 xf = *(const u32x4*)(abase + (k0 + j) * 32);
-        if (!row0) xf = u32x4{0u, 0u, 0u, 0u};
-        acc = mfma16(__builtin_bit_cast(bf16x8, xf), __builtin_bit_cast(bf16x8, wf), acc);
-        wait_lgkm0();
-        issue(slot);
-        slot = slot + 1 == kRing ? 0 : slot + 1;
+      const int2 e = mytab[p_i++];
+      p_ptr = p_base + (long long)__builtin_amdgcn_readfirstlane(e.x) * kUnit;
+      p_left = __builtin_amdgcn_readfirstlane(e.y);
+    };
+    auto issue = [&](int sl) {
+      __builtin_amdgcn_global_load_lds(GP(p_ptr + lane), LP(myring + sl * 64), 16, 0, 2);
+      if (p_left > 0) {
+        if (--p_left > 0)
+          p_ptr += 64;
+        else
+          settle();
       }
-      if (lane < 16) red[(wv * kDecodeMaxSeg + s) * 16 + lane] = acc[0];
+    };
+    if (streams) {
+      settle();
+  #pragma unroll 1
+      for (int f = 0; f < kRing; ++f) issue(f);
     }
-    if (nk == 0)   // a wave without k steps contributes zeros
-      for (int s = lane; s < nseg * 16; s += 64) red[wv * kDecodeMaxSeg * 16 + s] = 0.f;
-  };
 
-  // Synchronising wave: grid barrier; every wave then reads the outcome.
-  unsigned nbar = 0;
-  auto barrier = [&]() -> bool {
-    if (syncw) {
-      const bool ok = grid_sync(a, ++nbar);
-      if (lane == 0) s_ok = ok;
-    }
-    block_sync();
-    return s_ok != 0;
-  };
-
-  unsigned nhbar = 0;
-  const float* gains = a.gains;
-  int tok = 0;   // synchronising wave: the token this pass starts from
-  for (int pass = 0; pass < a.n_pass; ++pass) {
-  const int pos = a.pos + pass;
-  // Prologue: each workgroup writes its down-projection outputs' share of the
-  // token's embedding row (ids clamped into [0, V)).  First pass: clear the
-  // accumulator for the first layer's step 2 (the last layer's step 4 leaves
-  // it clear for the next pass); check that this workgroup runs on XCD
-  // blockIdx % 8, which makes each head's workgroups share one L2.
-  if (syncw) {
-    if (pass == 0 || a.forced) tok = a.tok_in[pass];
-    const bf16* er = a.embed + (size_t)min(max(tok, 0), a.V - 1) * d;
-    for (int i = lane; i < DH / 2; i += 64) rp[i] = a.rope[(size_t)pos * (DH / 2) + i];
-    for (int e = db0 * 16 + lane; e < (db0 + nseg3) * 16; e += 64) {
-      st_f32(r_x, e * 4, bf2f(er[e]));
-      if (pass == 0) st_u64(r_acc, e * 8, 0ull);
-    }
-    if (pass == 0 && lane == 0 && (__builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xf) != (unsigned)(gi & 7))
-      __hip_atomic_store(a.bar + kDecodeXccWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  const bool run = barrier();
-  const bool xl = H % 8 == 0 &&
-                  __hip_atomic_load(a.bar + kDecodeXccWord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
-  int layers_done = 0;
-  for (int l = 0; l < a.L && run; ++l) {
-    bf16* const lkc = a.kc + (size_t)l * a.kv_layer_elems;
-    bf16* const lvc = a.vc + (size_t)l * a.kv_layer_elems;
-    // ---------------- 1. QKV projection (head ah's rows, published to the head's workgroups)
-    stage_norm<false, NCH>(r_x, r_x, a.bar, gains + (size_t)l * 2 * d, d, a.KBd * 32, a.eps, act, wred);
-    block_sync();
-    if (!syncw) run_step(kUnQkv, nseg0, nkd, k0d);
-    if (syncw && attn && (a.flags & kDecodeWarmKv)) {
-      // share asl of head ah's cached keys (rows of DH) and values (dims of
-      // kv_pad), read once now so that step 2 finds them in this XCD's L2
-      const char* kb = reinterpret_cast<const char*>(lkc + (size_t)ah * a.kv_pad * DH);
-      const char* vb = reinterpret_cast<const char*>(lvc + (size_t)ah * DH * a.kv_pad);
-      const int r0 = asl * pos / nsl, r1 = (asl + 1) * pos / nsl;
-      for (int o = r0 * DH * 2 + lane * 16; o < r1 * DH * 2; o += 1024)
-        __builtin_amdgcn_global_load_lds(GP(kb + o), LP(sink), 16, 0, 0);
-      for (int dm = asl * DH / nsl; dm < (asl + 1) * DH / nsl; ++dm)
-        for (int o = lane * 16; o < pos * 2; o += 1024)
-          __builtin_amdgcn_global_load_lds(GP(vb + (size_t)dm * a.kv_pad * 2 + o), LP(sink), 16, 0, 0);
-    }
-    block_sync();
-    if (attn) {
-      if (syncw) {
-        for (int s0 = 0; s0 < nseg0; s0 += 4) {
-          const int s = s0 + (lane >> 4), t = lane & 15;
-          if (s < nseg0) {
-            const int m = s / nbm, rb = qb0 + s - m * nbm;
-            st_f32_x(r_qkv, (m * d + rb * 16 + t) * 4, sum_partials(red, s, t), xl);
-          }
-        }
-        const bool ok = head_sync(a, ah, (unsigned)nsl, ++nhbar);
-        if (lane == 0) s_ok = ok;
-      }
-      block_sync();
-      if (!s_ok) break;
-
-      // ---------------- 2. attention of head ah, times W_o's slice asl of head-ah columns
-      attn_head<DH>(ah, pos, d, a.kv_pad, asl == 0, xl, lkc, lvc, rp, r_qkv, qs, kn, vn, wred, sc, act);
-      if (!syncw) run_step(kUnO, nseg_o, KH, 0);
-      block_sync();
-      if (syncw) {
-        bool bad = false;
-        for (int w = 0; w < kWaves; ++w) {
-          const int wb0 = w * nsb / kWaves, wn = (w + 1) * nsb / kWaves - wb0;
-          for (int s0 = 0; s0 < wn; s0 += 4) {
-            const int s = s0 + (lane >> 4), t = lane & 15;
-            if (s < wn) {
-              const float cv = red[(w * kDecodeMaxSeg + s) * 16 + t];
-              if (fabsf(cv) < kFixLimit)
-                __hip_atomic_fetch_add(a.racc + (sb0 + wb0 + s) * 16 + t,
-                                       (unsigned long long)__float2ll_rn(cv * kFixScale), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-              else
-                bad = true;
+    // Compute waves: nseg blocks of nk k steps each over the staged activation
+    // (k steps k0.. of act); partial sums to red[wave][block].  Fragments are
+    // consumed UN at a time: the UN oldest ring loads have landed, their LDS
+    // reads overlap, then their slots are refilled.  A step whose fragments
+    // are already in the ring (the output projection after the attention) is
+    // bound by this loop, not by HBM.
+    // NEWER: loads issued after the ring's present fragments (the keys and values
+    // of step 2), which the first kRing waits leave outstanding.
+    auto run_step = [&](auto un, auto newer, int nseg, int nk, int k0) {
+      constexpr int UN = decltype(un)::value, NEWER = decltype(newer)::value;
+      int old = NEWER > 0 ? kRing : 0;   // fragments still older than those loads
+      const bf16* abase = act + (lane >> 4) * 8;
+      const bool row0 = (lane & 15) == 0;
+      for (int s = 0; s < nseg; ++s) {
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        int j = 0;
+        if constexpr (UN > 1) {
+          for (; j + UN <= nk; j += UN) {
+            wait_vm<kRing - UN>();
+            u32x4 wf[UN], xf[UN];
+  #pragma unroll
+            for (int u = 0; u < UN; ++u) {
+              const int sl = slot + u < kRing ? slot + u : slot + u - kRing;
+              wf[u] = myring[sl * 64 + lane];
+              xf[u] = *(const u32x4*)(abase + (k0 + j + u) * 32);
+              if (!row0) xf[u] = u32x4{0u, 0u, 0u, 0u};
+            }
+  #pragma unroll
+            for (int u = 0; u < UN; ++u)
+              acc = mfma16(__builtin_bit_cast(bf16x8, xf[u]), __builtin_bit_cast(bf16x8, wf[u]), acc);
+            wait_lgkm0();
+  #pragma unroll
+            for (int u = 0; u < UN; ++u) {
+              issue(slot);
+              slot = slot + 1 == kRing ? 0 : slot + 1;
             }
           }
         }
-        if (bad) __hip_atomic_store(a.bar + kDecodePoisonWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
-    if (!barrier()) break;
-
-    // ---------------- 3. gate/up projection + SwiGLU
-    stage_norm<true, NCH>(r_x, r_acc, a.bar, gains + (size_t)l * 2 * d + d, d, a.KBd * 32, a.eps, act, wred);
-    block_sync();
-    if (!syncw) run_step(kUnGu, nseg2, nkd, k0d);
-    block_sync();
-    if (syncw) {
-      for (int s0 = 0; s0 < nseg2 / 2; s0 += 4) {
-        const int pr = s0 + (lane >> 4), t = lane & 15;
-        if (pr < nseg2 / 2) {
-          const float g = sum_partials(red, 2 * pr, t), u = sum_partials(red, 2 * pr + 1, t);
-          st_b16(r_act, ((gp0 + pr) * 16 + t) * 2, f2bf(g / (1.0f + __expf(-g)) * u));
+        for (; j < nk; ++j) {
+          if (NEWER > 0 && old > 0) {
+            wait_vm<kRing - 1 + NEWER>();
+            --old;
+          } else {
+            wait_vm<kRing - 1>();
+          }
+          const u32x4 wf = myring[slot * 64 + lane];
+          u32x4 xf = *(const u32x4*)(abase + (k0 + j) * 32);
+          if (!row0) xf = u32x4{0u, 0u, 0u, 0u};
+          acc = mfma16(__builtin_bit_cast(bf16x8, xf), __builtin_bit_cast(bf16x8, wf), acc);
+          wait_lgkm0();
+          issue(slot);
+          slot = slot + 1 == kRing ? 0 : slot + 1;
         }
+        if (lane < 16) red[(wv * kDecodeMaxSeg + s) * 16 + lane] = acc[0];
       }
-    }
-    if (!barrier()) break;
+      if (nk == 0)   // a wave without k steps contributes zeros
+        for (int s = lane; s < nseg * 16; s += 64) red[wv * kDecodeMaxSeg * 16 + s] = 0.f;
+    };
 
-    // ---------------- 4. down projection + residual; the accumulator is
-    // cleared for the next layer's step 2 (every workgroup staged r in step 3,
-    // before the last barrier)
-    stage_copy(r_act, F, a.KBf * 32, act);
-    block_sync();
-    if (!syncw) run_step(kUnDown, nseg3, nkf, k0f);
-    block_sync();
-    if (syncw) {
-      const bool poisoned = poisoned_now(a.bar);
-      for (int s0 = 0; s0 < nseg3; s0 += 4) {
-        const int s = s0 + (lane >> 4), t = lane & 15;
-        if (s < nseg3) {
-          const int e = (db0 + s) * 16 + t;
-          const float rv = res_value(ld_f32(r_x, e * 4), ld_u64(r_acc, e * 8), poisoned);
-          st_f32(r_x, e * 4, rv + sum_partials(red, s, t));
-          st_u64(r_acc, e * 8, 0ull);
+    bool ok = true;
+    for (int pass = 0; pass < a.n_pass && ok; ++pass) {
+      const int pos = a.pos + pass;
+      block_sync();
+      if (!s_ok) break;
+      for (int l = 0; l < a.L; ++l) {
+        ok = false;
+        bf16* const lkc = a.kc + (size_t)l * a.kv_layer_elems;
+        bf16* const lvc = a.vc + (size_t)l * a.kv_layer_elems;
+        const float* const gains = a.gains + (size_t)l * 2 * d;
+        u16x8 kv[kKvLoads], vv[kKvLoads];
+        // ---------------- 1. QKV projection (head ah's rows).  The head's first
+        // cached keys and values are in flight through it; the barrier's
+        // memory clobber keeps their loads here.
+        stage_norm<false, NCH>(r_x, r_x, a.bar, gains, d, a.KBd * 32, a.eps, act, wred);
+        if (attn) attn_load<DH>(ah, pos, a.kv_pad, lkc, lvc, kv, vv);
+        block_sync();
+        run_step(kUnQkv, std::integral_constant<int, 2 * kKvLoads>{}, nseg0, nkd, k0d);
+        block_sync();
+        if (attn) {
+          block_sync();
+          if (!s_ok) break;
+          // ---------------- 2. attention of head ah, times W_o's slice asl of head-ah columns
+          attn_compute<DH>(ah, pos, a.kv_pad, lkc, lvc, qs, kn, vn, wred, sc, act, kv, vv);
+          run_step(kUnO, kNone, nseg_o, KH, 0);
+          block_sync();
         }
+        block_sync();
+        if (!s_ok) break;
+        // ---------------- 3. gate/up projection
+        stage_norm<true, NCH>(r_x, r_acc, a.bar, gains + d, d, a.KBd * 32, a.eps, act, wred);
+        block_sync();
+        run_step(kUnGu, kNone, nseg2, nkd, k0d);
+        block_sync();
+        block_sync();
+        if (!s_ok) break;
+        // ---------------- 4. down projection
+        stage_copy(r_act, F, a.KBf * 32, act);
+        block_sync();
+        run_step(kUnDown, kNone, nseg3, nkf, k0f);
+        block_sync();
+        block_sync();
+        if (!s_ok) break;
+        ok = true;
+      }
+      if (ok && head) {
+        // ---------------- 5. final RMSNorm and LM head
+        stage_norm<false, NCH>(r_x, r_x, a.bar, a.final_gain, d, a.KBd * 32, a.eps, act, wred);
+        block_sync();
+        run_step(kUnQkv, kNone, nh, nkd, k0d);
+        block_sync();
+        block_sync();
+        ok = s_ok != 0;
       }
     }
-    if (!barrier()) break;
-    layers_done = l + 1;
-  }
+  } else {
+    const rsrc_t r_qkv = rsrc(a.qkv, (size_t)3 * d * 4);
+    unsigned nbar = 0, nhbar = 0;
+    // grid barrier; the compute waves read the outcome after the block barrier
+    auto barrier = [&]() -> bool {
+      const bool done = grid_sync(a, ++nbar);
+      if (lane == 0) s_ok = done;
+      block_sync();
+      return done;
+    };
+    int tok = 0;   // the token this pass starts from
+    bool ok = true;
+    for (int pass = 0; pass < a.n_pass && ok; ++pass) {
+      const int pos = a.pos + pass;
+      // Prologue: each workgroup writes its down-projection outputs' share of
+      // the token's embedding row (ids clamped into [0, V)).  First pass:
+      // clear the accumulator for the first layer's step 2 (the last layer's
+      // step 4 leaves it clear for the next pass); check that this workgroup
+      // runs on XCD blockIdx % 8, which makes each head's workgroups share
+      // one L2.
+      {
+        if (pass == 0 || a.forced) tok = a.tok_in[pass];
+        const bf16* er = a.embed + (size_t)min(max(tok, 0), a.V - 1) * d;
+        for (int i = lane; i < DH / 2; i += 64) rp[i] = a.rope[(size_t)pos * (DH / 2) + i];
+        for (int e = db0 * 16 + lane; e < (db0 + nseg3) * 16; e += 64) {
+          st_f32(r_x, e * 4, bf2f(er[e]));
+          if (pass == 0) st_u64(r_acc, e * 8, 0ull);
+        }
+        if (pass == 0 && lane == 0 && (__builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xf) != (unsigned)(gi & 7))
+          __hip_atomic_store(a.bar + kDecodeXccWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (!barrier()) break;
+      const bool xl = H % 8 == 0 &&
+                      __hip_atomic_load(a.bar + kDecodeXccWord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+      for (int l = 0; l < a.L; ++l) {
+        ok = false;
+        // ---------------- 1. q, k, v published to the head's workgroups
+        block_sync();   // in stage_norm
+        block_sync();
+        block_sync();   // partial sums ready
+        if (attn) {
+          for (int s0 = 0; s0 < nseg0; s0 += 4) {
+            const int s = s0 + (lane >> 4), t = lane & 15;
+            if (s < nseg0) {
+              const int m = s / nbm, rb = qb0 + s - m * nbm;
+              st_f32_x(r_qkv, (m * d + rb * 16 + t) * 4, sum_partials(red, s, t), xl);
+            }
+          }
+          const bool done = head_sync(a, ah, (unsigned)nsl, ++nhbar);
+          if (lane == 0) s_ok = done;
+          block_sync();
+          if (!done) break;
+          // ---------------- 2. new key and value; output projection's contributions
+          attn_sync<DH>(ah, pos, d, a.kv_pad, asl == 0, xl, a.kc + (size_t)l * a.kv_layer_elems,
+                        a.vc + (size_t)l * a.kv_layer_elems, rp, r_qkv, qs, kn, vn);
+          block_sync();
+          bool bad = false;
+          for (int w = 0; w < kWaves; ++w) {
+            const int wb0 = w * nsb / kWaves, wn = (w + 1) * nsb / kWaves - wb0;
+            for (int s0 = 0; s0 < wn; s0 += 4) {
+              const int s = s0 + (lane >> 4), t = lane & 15;
+              if (s < wn) {
+                const float cv = red[(w * kDecodeMaxSeg + s) * 16 + t];
+                if (fabsf(cv) < kFixLimit)
+                  __hip_atomic_fetch_add(a.racc + (sb0 + wb0 + s) * 16 + t,
+                                         (unsigned long long)__float2ll_rn(cv * kFixScale), __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+                else
+                  bad = true;
+              }
+            }
+          }
+          if (bad) __hip_atomic_store(a.bar + kDecodePoisonWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (!barrier()) break;
+        // ---------------- 3. SwiGLU
+        block_sync();   // in stage_norm
+        block_sync();
+        block_sync();   // partial sums ready
+        for (int s0 = 0; s0 < nseg2 / 2; s0 += 4) {
+          const int pr = s0 + (lane >> 4), t = lane & 15;
+          if (pr < nseg2 / 2) {
+            const float g = sum_partials(red, 2 * pr, t), u = sum_partials(red, 2 * pr + 1, t);
+            st_b16(r_act, ((gp0 + pr) * 16 + t) * 2, f2bf(g / (1.0f + __expf(-g)) * u));
+          }
+        }
+        if (!barrier()) break;
+        // ---------------- 4. residual; the accumulator is cleared for the next
+        // layer's step 2 (every workgroup staged r in step 3, before the last
+        // barrier)
+        block_sync();
+        block_sync();   // partial sums ready
+        {
+          const bool poisoned = poisoned_now(a.bar);
+          for (int s0 = 0; s0 < nseg3; s0 += 4) {
+            const int s = s0 + (lane >> 4), t = lane & 15;
+            if (s < nseg3) {
+              const int e = (db0 + s) * 16 + t;
+              const float rv = res_value(ld_f32(r_x, e * 4), ld_u64(r_acc, e * 8), poisoned);
+              st_f32(r_x, e * 4, rv + sum_partials(red, s, t));
+              st_u64(r_acc, e * 8, 0ull);
+            }
+          }
+        }
+        if (!barrier()) break;
+        ok = true;
+      }
+      if (!ok || !head) continue;
 
-  if (layers_done != a.L) break;   // a barrier timed out
-
-  // ---------------- 5. final RMSNorm, LM head, and this pass's greedy token
-  // and margin (Eq. 1): each workgroup writes its logits and one partial
-  // record (max, sum of exp, top two bins) of them; after a grid barrier
-  // workgroup 0 merges the records in workgroup order (the merge is the same
-  // on every run) and writes the token and the margin; the others merge them
-  // for the token only, when the next pass starts from it.
-  if (head) {
-    stage_norm<false, NCH>(r_x, r_x, a.bar, a.final_gain, d, a.KBd * 32, a.eps, act, wred);
-    block_sync();
-    if (!syncw) run_step(kUnQkv, nh, nkd, k0d);
-    block_sync();
-    const rsrc_t r_hp = rsrc(a.head_part, (size_t)G * 8 * 4);
-    if (syncw) {
-      const rsrc_t r_lg = rsrc(a.logits + pass * a.logits_stride, (size_t)a.V * 4);
-      const int lo = a.full_vocab ? 0 : a.bin_lo;
+      // ---------------- 5. this pass's greedy token and margin (Eq. 1): each
+      // workgroup writes its logits and one partial record (max, sum of exp,
+      // top two bins) of them; after a grid barrier workgroup 0 merges the
+      // records in workgroup order (the merge is the same on every run) and
+      // writes the token and the margin; the others merge them for the token
+      // only, when the next pass starts from it.
+      block_sync();   // in stage_norm
+      block_sync();
+      block_sync();   // partial sums ready
+      const rsrc_t r_hp = rsrc(a.head_part, (size_t)G * 8 * 4);
       float mx = -INFINITY, sm = 0.f, v1 = -INFINITY, v2 = -INFINITY;
       int i1 = 0x7fffffff, i2 = 0x7fffffff;
-      for (int s0 = 0; s0 < nh; s0 += 4) {
-        const int s = s0 + (lane >> 4), t = lane & 15, idx = (hb0 + s) * 16 + t;
-        if (s < nh && idx < a.V) {
-          const float z = sum_partials(red, s, t);
-          st_f32(r_lg, idx * 4, z);
-          if (idx >= lo) lse_add(mx, sm, z);
-          if (idx >= a.bin_lo) top2_add(v1, i1, v2, i2, z, idx);
+      auto merge_wave = [&]() {
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) {
+          lse_merge(mx, sm, __shfl_xor(mx, m), __shfl_xor(sm, m));
+          const float w1 = __shfl_xor(v1, m), w2 = __shfl_xor(v2, m);
+          const int j1 = __shfl_xor(i1, m), j2 = __shfl_xor(i2, m);
+          top2_add(v1, i1, v2, i2, w1, j1);
+          top2_add(v1, i1, v2, i2, w2, j2);
+        }
+      };
+      {
+        const rsrc_t r_lg = rsrc(a.logits + pass * a.logits_stride, (size_t)a.V * 4);
+        const int lo = a.full_vocab ? 0 : a.bin_lo;
+        for (int s0 = 0; s0 < nh; s0 += 4) {
+          const int s = s0 + (lane >> 4), t = lane & 15, idx = (hb0 + s) * 16 + t;
+          if (s < nh && idx < a.V) {
+            const float z = sum_partials(red, s, t);
+            st_f32(r_lg, idx * 4, z);
+            if (idx >= lo) lse_add(mx, sm, z);
+            if (idx >= a.bin_lo) top2_add(v1, i1, v2, i2, z, idx);
+          }
+        }
+        merge_wave();
+        if (lane < 6) {
+          const float rec[6] = {mx, sm, v1, __int_as_float(i1), v2, __int_as_float(i2)};
+          st_f32(r_hp, (gi * 8 + lane) * 4, rec[lane]);
         }
       }
-#pragma unroll
-      for (int m = 1; m < 64; m <<= 1) {
-        lse_merge(mx, sm, __shfl_xor(mx, m), __shfl_xor(sm, m));
-        const float w1 = __shfl_xor(v1, m), w2 = __shfl_xor(v2, m);
-        const int j1 = __shfl_xor(i1, m), j2 = __shfl_xor(i2, m);
-        top2_add(v1, i1, v2, i2, w1, j1);
-        top2_add(v1, i1, v2, i2, w2, j2);
-      }
-      if (lane < 6) {
-        const float rec[6] = {mx, sm, v1, __int_as_float(i1), v2, __int_as_float(i2)};
-        st_f32(r_hp, (gi * 8 + lane) * 4, rec[lane]);
-      }
-    }
-    if (!barrier()) break;
-    if (syncw && (gi == 0 || (!a.forced && pass + 1 < a.n_pass))) {
-      float mx = -INFINITY, sm = 0.f, v1 = -INFINITY, v2 = -INFINITY;
-      int i1 = 0x7fffffff, i2 = 0x7fffffff;
-      for (int w = lane; w < G; w += 64) {
-        lse_merge(mx, sm, ld_f32(r_hp, (w * 8) * 4), ld_f32(r_hp, (w * 8 + 1) * 4));
-        top2_add(v1, i1, v2, i2, ld_f32(r_hp, (w * 8 + 2) * 4), __float_as_int(ld_f32(r_hp, (w * 8 + 3) * 4)));
-        top2_add(v1, i1, v2, i2, ld_f32(r_hp, (w * 8 + 4) * 4), __float_as_int(ld_f32(r_hp, (w * 8 + 5) * 4)));
-      }
-#pragma unroll
-      for (int m = 1; m < 64; m <<= 1) {
-        lse_merge(mx, sm, __shfl_xor(mx, m), __shfl_xor(sm, m));
-        const float w1 = __shfl_xor(v1, m), w2 = __shfl_xor(v2, m);
-        const int j1 = __shfl_xor(i1, m), j2 = __shfl_xor(i2, m);
-        top2_add(v1, i1, v2, i2, w1, j1);
-        top2_add(v1, i1, v2, i2, w2, j2);
-      }
-      tok = i1;   // the same in every lane and workgroup: the top two are merged under a total order
-      if (gi == 0 && lane == 0) {
-        a.tok_out[pass] = i1;
-        a.margin_out[pass] = (__expf(v1 - mx) - __expf(v2 - mx)) / sm;
+      ok = barrier();
+      if (ok && (gi == 0 || (!a.forced && pass + 1 < a.n_pass))) {
+        mx = -INFINITY; sm = 0.f; v1 = -INFINITY; v2 = -INFINITY;
+        i1 = i2 = 0x7fffffff;
+        for (int w = lane; w < G; w += 64) {
+          lse_merge(mx, sm, ld_f32(r_hp, (w * 8) * 4), ld_f32(r_hp, (w * 8 + 1) * 4));
+          top2_add(v1, i1, v2, i2, ld_f32(r_hp, (w * 8 + 2) * 4), __float_as_int(ld_f32(r_hp, (w * 8 + 3) * 4)));
+          top2_add(v1, i1, v2, i2, ld_f32(r_hp, (w * 8 + 4) * 4), __float_as_int(ld_f32(r_hp, (w * 8 + 5) * 4)));
+        }
+        merge_wave();
+        tok = i1;   // the same in every lane and workgroup: the top two are merged under a total order
+        if (gi == 0 && lane == 0) {
+          a.tok_out[pass] = i1;
+          a.margin_out[pass] = (__expf(v1 - mx) - __expf(v2 - mx)) / sm;
+        }
       }
     }
   }
-  }   // passes
   wait_vm<0>();   // direct-to-LDS loads must land before the workgroup ends
 }
 
