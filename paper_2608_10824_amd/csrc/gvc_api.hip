@@ -1213,8 +1213,6 @@ int32_t gvc_decode_actions(gvc_ctx* c, int32_t* tokens_out, float* margins_out, 
     if (c->persist) {
       // every barrier word but the abort word, which stays set until a gate reports it
       HIP_TRY(launch_fill_u32(c->K<uint32_t>(p.bar_off), 0u, kDecodeAbortWord, s));
-      HIP_TRY(launch_fill_u32(c->K<uint32_t>(p.bar_off) + kDecodeAbortWord + 1, 0u,
-                              kDecodeBarWords - kDecodeAbortWord - 1, s));
     }
     // The single-launch decode runs all D - 1 passes at once when it also
     // chooses the tokens; else one pass per launch.

@@ -8,15 +8,15 @@ namespace gvc {
 // One single-token pass over all layers for one episode (k_decode.hip).
 constexpr int kDecodeMaxSeg = 8;       // weight blocks per workgroup per step
 constexpr int kDecodeMaxSegs = 5 * kDecodeMaxSeg;   // of a wave in one layer (4 steps) and the LM head
-constexpr int kDecodeAbortWord = 512;  // barrier words: abort flag
 constexpr int kDecodeXccWord = 544;    // barrier words: set when a workgroup is not on XCD blockIdx % 8
 constexpr int kDecodePoisonWord = 576; // barrier words: set when a head contribution was not finite
 constexpr int kDecodeHeadWord = 1024;  // barrier words: per-head counters, 32 words apart
 constexpr int kDecodeMaxHeads = 64;
 constexpr int kDecodeMaxGrid = 1024;   // workgroups of one pass (per-workgroup head records)
-// zeroed before a launch sequence, except the abort word, which stays set
-// until the gate that follows has reported it
-constexpr int kDecodeBarWords = kDecodeHeadWord + 32 * kDecodeMaxHeads;
+// The abort flag is the last barrier word: the others are zeroed before a launch
+// sequence, it stays set until the gate that follows has reported it.
+constexpr int kDecodeAbortWord = kDecodeHeadWord + 32 * kDecodeMaxHeads;
+constexpr int kDecodeBarWords = kDecodeAbortWord + 1;
 // grid barriers and per-head barriers of one pass over L layers (one more
 // grid barrier when the pass also runs the LM head and the token choice)
 constexpr int decode_grid_barriers(int L, bool head) { return 1 + 3 * L + (head ? 1 : 0); }

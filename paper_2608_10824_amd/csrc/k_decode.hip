@@ -79,9 +79,7 @@ constexpr int kSC0 = 1;                        // buffer cache policy: coherent 
 constexpr int kRingBytes = kWaves * kRing * 1024;
 constexpr int kRedBytes = kWaves * kDecodeMaxSeg * 16 * 4;
 constexpr int kScoreOffset = 256;              // attention scores follow the head output in the act region
-// ring fragments consumed per round in each step (see run_step)
-constexpr std::integral_constant<int, 1> kUnQkv{}, kUnGu{}, kUnDown{};
-constexpr std::integral_constant<int, 2> kUnO{};
+constexpr int kUn = 2;   // ring fragments consumed per round (see run_step)
 constexpr std::integral_constant<int, 0> kNone{};
 // Key and value loads a compute thread keeps in flight through step 1 (16
 // bytes each): with head dimension 128 they hold the first 288 keys and values
@@ -137,6 +135,12 @@ __device__ __forceinline__ void st_f32_x(rsrc_t r, int off, float v, bool xl) {
 __device__ __forceinline__ u16x8 ld_plain_b128(rsrc_t r, int off) {
   return __builtin_bit_cast(u16x8, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }
+// A new key or value.  Every workgroup of the head stores all of them itself:
+// the passes that follow in this launch read them back through the CU's own
+// caches, where a copy of the line from before the store of another workgroup
+// could stay (in the L1, or in the L2 of another XCD).  The copies are the
+// same bytes, and go to memory from each L2 at the end of the launch.
+__device__ __forceinline__ void st_kv(rsrc_t r, int off, bf16 v) { __builtin_amdgcn_raw_buffer_store_b16(v, r, off, 0, 0); }
 __device__ __forceinline__ void st_f32(rsrc_t r, int off, float v) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, kSC1);
 }
@@ -352,11 +356,11 @@ __device__ __forceinline__ void attn_load(int h, int pos, int kv_pad, bf16* lkc,
 // of the head's workgroups in full (they share the head's cache lines in
 // one L2); the output (DH values, bf16) goes to oact in LDS.
 //
-// The synchronising wave's part: RoPE of the new q and k, and, when `append`,
-// the new key and value into the caches (for later passes).  Position pos
-// itself is read from LDS.  Joins the four block barriers of attn_compute.
+// The synchronising wave's part: RoPE of the new q and k, and the new key
+// and value into the caches (for later passes).  Position pos itself is read
+// from LDS.  Joins the four block barriers of attn_compute.
 template <int DH>
-__device__ __forceinline__ void attn_sync(int h, int pos, int d, int kv_pad, bool append, bool xl, bf16* lkc, bf16* lvc,
+__device__ __forceinline__ void attn_sync(int h, int pos, int d, int kv_pad, bool xl, bf16* lkc, bf16* lvc,
                                           const float2* rp, rsrc_t r_qkv, float* qs, float* kn, float* vn) {
   const int lane = threadIdx.x & 63;
   constexpr int half = DH / 2;
@@ -385,10 +389,8 @@ __device__ __forceinline__ void attn_sync(int h, int pos, int d, int kv_pad, boo
       const bf16 ka = f2bf(k0[n] * cs.x - k1[n] * cs.y), kb = f2bf(k1[n] * cs.x + k0[n] * cs.y);
       kn[i] = bf2f(ka);
       kn[i + half] = bf2f(kb);
-      if (append) {
-        st_b16(r_k, (pos * DH + i) * 2, ka);
-        st_b16(r_k, (pos * DH + i + half) * 2, kb);
-      }
+      st_kv(r_k, (pos * DH + i) * 2, ka);
+      st_kv(r_k, (pos * DH + i + half) * 2, kb);
     }
   }
 #pragma unroll
@@ -397,7 +399,7 @@ __device__ __forceinline__ void attn_sync(int h, int pos, int d, int kv_pad, boo
     if (i < DH) {
       const bf16 v = f2bf(vr[n]);
       vn[i] = bf2f(v);
-      if (append) st_b16(r_v, (i * kv_pad + pos) * 2, v);
+      st_kv(r_v, (i * kv_pad + pos) * 2, v);
     }
   }
   block_sync();
@@ -624,57 +626,59 @@ __global__ __launch_bounds__(kThreads) void k_decode_pass(const DecodeArgs a) {
 
     // Compute waves: nseg blocks of nk k steps each over the staged activation
     // (k steps k0.. of act); partial sums to red[wave][block].  Fragments are
-    // consumed UN at a time: the UN oldest ring loads have landed, their LDS
-    // reads overlap, then their slots are refilled.  A step whose fragments
-    // are already in the ring (the output projection after the attention) is
-    // bound by this loop, not by HBM.
-    // NEWER: loads issued after the ring's present fragments (the keys and values
-    // of step 2), which the first kRing waits leave outstanding.
-    auto run_step = [&](auto un, auto newer, int nseg, int nk, int k0) {
-      constexpr int UN = decltype(un)::value, NEWER = decltype(newer)::value;
+    // consumed kUn at a time: the oldest ring loads have landed, their LDS
+    // reads overlap, then their slots are refilled (7B: 2722 us per pass one
+    // at a time, 2712 by two).
+    // All 16 rows of the MFMA's A operand hold the activation (the lanes of a
+    // row read one address); only row 0 of the result is used.
+    // NEWER: loads issued after the ring's present fragments (the keys and
+    // values of step 2), which the first kRing waits leave outstanding.
+    auto run_step = [&](auto newer, int nseg, int nk, int k0) __attribute__((always_inline)) {
+      constexpr int NEWER = decltype(newer)::value;
       int old = NEWER > 0 ? kRing : 0;   // fragments still older than those loads
       const bf16* abase = act + (lane >> 4) * 8;
-      const bool row0 = (lane & 15) == 0;
       for (int s = 0; s < nseg; ++s) {
         floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-        int j = 0;
-        if constexpr (UN > 1) {
-          for (; j + UN <= nk; j += UN) {
+        auto batch = [&](auto un, int j) __attribute__((always_inline)) {
+          constexpr int UN = decltype(un)::value;
+          if (NEWER > 0 && old >= UN) {
+            wait_vm<kRing - UN + NEWER>();
+            old -= UN;
+          } else {
             wait_vm<kRing - UN>();
-            u32x4 wf[UN], xf[UN];
-  #pragma unroll
+            old = 0;
+          }
+          u32x4 wf[UN], xf[UN];
+#pragma unroll
+          for (int u = 0; u < UN; ++u) {
+            const int sl = slot + u < kRing ? slot + u : slot + u - kRing;
+            wf[u] = myring[sl * 64 + lane];
+            xf[u] = *(const u32x4*)(abase + (k0 + j + u) * 32);
+          }
+#pragma unroll
+          for (int u = 0; u < UN; ++u)
+            acc = mfma16(__builtin_bit_cast(bf16x8, xf[u]), __builtin_bit_cast(bf16x8, wf[u]), acc);
+          wait_lgkm0();   // the reads have left the slots before they are refilled
+          if (UN > 1 && p_left > UN) {
+#pragma unroll
             for (int u = 0; u < UN; ++u) {
               const int sl = slot + u < kRing ? slot + u : slot + u - kRing;
-              wf[u] = myring[sl * 64 + lane];
-              xf[u] = *(const u32x4*)(abase + (k0 + j + u) * 32);
-              if (!row0) xf[u] = u32x4{0u, 0u, 0u, 0u};
+              __builtin_amdgcn_global_load_lds(GP(p_ptr + u * 64 + lane), LP(myring + sl * 64), 16, 0, 2);
             }
-  #pragma unroll
-            for (int u = 0; u < UN; ++u)
-              acc = mfma16(__builtin_bit_cast(bf16x8, xf[u]), __builtin_bit_cast(bf16x8, wf[u]), acc);
-            wait_lgkm0();
-  #pragma unroll
+            p_ptr += UN * 64;
+            p_left -= UN;
+            slot = slot + UN < kRing ? slot + UN : slot + UN - kRing;
+          } else {
+#pragma unroll 1
             for (int u = 0; u < UN; ++u) {
               issue(slot);
               slot = slot + 1 == kRing ? 0 : slot + 1;
             }
           }
-        }
-        for (; j < nk; ++j) {
-          if (NEWER > 0 && old > 0) {
-            wait_vm<kRing - 1 + NEWER>();
-            --old;
-          } else {
-            wait_vm<kRing - 1>();
-          }
-          const u32x4 wf = myring[slot * 64 + lane];
-          u32x4 xf = *(const u32x4*)(abase + (k0 + j) * 32);
-          if (!row0) xf = u32x4{0u, 0u, 0u, 0u};
-          acc = mfma16(__builtin_bit_cast(bf16x8, xf), __builtin_bit_cast(bf16x8, wf), acc);
-          wait_lgkm0();
-          issue(slot);
-          slot = slot + 1 == kRing ? 0 : slot + 1;
-        }
+        };
+        int j = 0;
+        for (; j + kUn <= nk; j += kUn) batch(std::integral_constant<int, kUn>{}, j);
+        for (; j < nk; ++j) batch(std::integral_constant<int, 1>{}, j);
         if (lane < 16) red[(wv * kDecodeMaxSeg + s) * 16 + lane] = acc[0];
       }
       if (nk == 0)   // a wave without k steps contributes zeros
@@ -698,14 +702,14 @@ __global__ __launch_bounds__(kThreads) void k_decode_pass(const DecodeArgs a) {
         stage_norm<false, NCH>(r_x, r_x, a.bar, gains, d, a.KBd * 32, a.eps, act, wred);
         if (attn) attn_load<DH>(ah, pos, a.kv_pad, lkc, lvc, kv, vv);
         block_sync();
-        run_step(kUnQkv, std::integral_constant<int, 2 * kKvLoads>{}, nseg0, nkd, k0d);
+        run_step(std::integral_constant<int, 2 * kKvLoads>{}, nseg0, nkd, k0d);
         block_sync();
         if (attn) {
           block_sync();
           if (!s_ok) break;
           // ---------------- 2. attention of head ah, times W_o's slice asl of head-ah columns
           attn_compute<DH>(ah, pos, a.kv_pad, lkc, lvc, qs, kn, vn, wred, sc, act, kv, vv);
-          run_step(kUnO, kNone, nseg_o, KH, 0);
+          run_step(kNone, nseg_o, KH, 0);
           block_sync();
         }
         block_sync();
@@ -713,14 +717,14 @@ __global__ __launch_bounds__(kThreads) void k_decode_pass(const DecodeArgs a) {
         // ---------------- 3. gate/up projection
         stage_norm<true, NCH>(r_x, r_acc, a.bar, gains + d, d, a.KBd * 32, a.eps, act, wred);
         block_sync();
-        run_step(kUnGu, kNone, nseg2, nkd, k0d);
+        run_step(kNone, nseg2, nkd, k0d);
         block_sync();
         block_sync();
         if (!s_ok) break;
         // ---------------- 4. down projection
         stage_copy(r_act, F, a.KBf * 32, act);
         block_sync();
-        run_step(kUnDown, kNone, nseg3, nkf, k0f);
+        run_step(kNone, nseg3, nkf, k0f);
         block_sync();
         block_sync();
         if (!s_ok) break;
@@ -730,7 +734,7 @@ __global__ __launch_bounds__(kThreads) void k_decode_pass(const DecodeArgs a) {
         // ---------------- 5. final RMSNorm and LM head
         stage_norm<false, NCH>(r_x, r_x, a.bar, a.final_gain, d, a.KBd * 32, a.eps, act, wred);
         block_sync();
-        run_step(kUnQkv, kNone, nh, nkd, k0d);
+        run_step(kNone, nh, nkd, k0d);
         block_sync();
         block_sync();
         ok = s_ok != 0;
@@ -789,7 +793,7 @@ __global__ __launch_bounds__(kThreads) void k_decode_pass(const DecodeArgs a) {
           block_sync();
           if (!done) break;
           // ---------------- 2. new key and value; output projection's contributions
-          attn_sync<DH>(ah, pos, d, a.kv_pad, asl == 0, xl, a.kc + (size_t)l * a.kv_layer_elems,
+          attn_sync<DH>(ah, pos, d, a.kv_pad, xl, a.kc + (size_t)l * a.kv_layer_elems,
                         a.vc + (size_t)l * a.kv_layer_elems, rp, r_qkv, qs, kn, vn);
           block_sync();
           bool bad = false;

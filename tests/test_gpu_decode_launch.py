@@ -42,3 +42,44 @@ def test_free_and_given_tokens_agree(cfg_fn, n_decode):
     moved = decode(other)
     assert torch.equal(moved[2][:, 0], free[2][:, 0]) and not torch.equal(moved[2][:, 1], free[2][:, 1])
     s.close()
+
+
+@pytest.mark.parametrize("heads,head_dim", [(4, 64), (8, 64), (3, 128), (5, 128)])
+def test_keys_and_values_of_another_decode_leave_no_trace(heads, head_dim):
+    """Every pass appends a key and a value that the next passes of the same
+    launch read back.  A decode of other tokens before this one leaves other
+    keys and values at the same places: the results must equal those of a
+    session that never ran it (heads on one compute die, or spread over
+    several), bit for bit, and the per-step launches' within rounding."""
+    import os
+    from paper_2608_10824_amd.session import Session
+    d = heads * head_dim if (heads * head_dim) % 256 == 0 else None
+    cfg = synth.config_c1().with_(n_heads=heads, d_model=d or 256 * heads, n_decode=16)
+    if not d:
+        cfg = cfg.with_(n_heads=heads * 2)   # d a multiple of 256 keeps the single launch
+    w = synth.model_weights(cfg, device=DEV)
+    si = synth.step_inputs(cfg, cfg.n_patches // 2)
+    fp, ids = si["frame_prev"].to(DEV), si["text_ids"].to(DEV)
+    g = torch.Generator().manual_seed(heads)
+    a, b = (torch.randint(0, cfg.vocab, (1, cfg.n_decode), generator=g, dtype=torch.int32).to(DEV) for _ in range(2))
+
+    def decode(s, forced):
+        s.step_prefill(fp, ids)
+        t, m, lg = s.decode_actions(logits=True, forced_tokens=forced)
+        torch.cuda.synchronize()
+        return t.clone(), m.clone(), lg.clone()
+
+    s1, s2 = Session(cfg, w, device=DEV), Session(cfg, w, device=DEV)
+    os.environ["GVC_DECODE"] = "legacy"
+    try:
+        s3 = Session(cfg, w, device=DEV)
+    finally:
+        del os.environ["GVC_DECODE"]
+    decode(s1, a)
+    got, ref, step = decode(s1, b), decode(s2, b), decode(s3, b)
+    for x, y in zip(got, ref):
+        assert torch.equal(x, y)
+    err = (got[2] - step[2]).norm(dim=-1) / step[2].norm(dim=-1)   # per position; bf16 roundings of two layers
+    assert float(err.max()) <= 2e-2, err
+    for s in (s1, s2, s3):
+        s.close()
