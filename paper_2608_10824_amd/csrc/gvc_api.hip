@@ -35,15 +35,11 @@ constexpr int kMaxNT = 5;   // token blocks per GEMM workgroup (best of 2..16 on
 // -> 12.5 us per launch; QKV equal, fc1 slower, 1 or 3 blocks slower).  A
 // row's result does not depend on the tile.
 constexpr int kVitNT = 2;
-constexpr int kBigRows = 1024;  // sessions with at least this many prompt rows use k_gemm_big
-// Split-k prompt-pass GEMMs (k_gemm_dx, or k_gemm_sk with GVC_SK_CORE=0) of
-// the sessions below kBigRows: k slices fixed per matrix shape.  Gate/up in 2
-// slices of 12-block groups, QKV in 4 slices of 12-block groups, the down
-// projection in 8 slices of 8-block groups (one weight block per compute
-// wave): at the 7B shape 230, 256 and 256 workgroups.  Inside the 7B prompt
-// pass at 148 rows this took the pass from 6.48 ms (per-pair kernels for QKV
-// and down, 16-block gate/up groups: 172 workgroups) to 5.72 ms; the output
-// projection stays on the per-pair kernel (8 slices measured 0.1 ms slower).
+constexpr int kBigRows = 1024;  // sessions with at least this many prompt rows sum every projection over k in one go
+// The other sessions sum a prompt-pass projection in k slices fixed per matrix
+// shape (gate/up 2, QKV 4, down 8, output the shares of tile_gemm), whichever
+// kernel runs it: split-k launches (k_gemm_dx) and the per-pair kernel for
+// few rows, the tile kernel (tile_gemm_wanted) for more.
 constexpr int kSkGuSlices = 2;
 constexpr int kSkQkvSlices = 4, kSkDownSlices = 8;
 
@@ -294,29 +290,25 @@ struct gvc_ctx {
   bool prefill_done = false;
   bool decode_done = false;
   int force_splits = 0;   // GVC_FORCE_SPLITS: waves splitting each GEMM's k range (4 or 8; testing)
-  int big_tw = 0;         // GVC_BIG_TW: tile height of the many-row kernel, 2, 3 or 4 token blocks per wave (testing)
+  int tile_shape = 0;     // GVC_BIG_TW: the tile kernel's shape of every launch, 1 .. 8 (testing; 0: chosen per launch)
   bool poison = false;    // GVC_POISON: arenas start as 0xFF bytes instead of zeros (testing)
   int validate = 0;       // GVC_VALIDATE: 1 = every prompt pass checks its row lists on the host, 2 = also
                           // alters the host copy first, so the check must fail (tests that it runs)
-  // prompt-pass projections on the many-row kernel: sessions of at least
-  // kBigRows prompt rows (B * P), for every pass of the session, so a row's
-  // result never depends on how many rows a pass recomputes; GVC_GEMM=big
-  // or small overrides (testing)
+  // prompt-pass projections on the tile kernel with one sum over k: sessions
+  // of at least kBigRows prompt rows (B * P), for every pass of the session, so
+  // a row's result never depends on how many rows a pass recomputes;
+  // GVC_GEMM=big or small overrides (testing)
   bool big_gemm = false;
-  // the other sessions' gate/up projection on the split-k kernel (GVC_SK=0
-  // turns it off: testing)
-  bool sk_gemm = true;
-  int sk_dx = 1;          // GVC_SK_CORE: split-k core, 1 = k_gemm_dx (decoupled streams), 0 = k_gemm_sk
-  // QKV and down projections of those sessions on the one-block-per-wave
-  // split-k shapes of the decoupled core (GVC_SK_QKV=0, GVC_SK_DOWN=0 turn
-  // them off)
-  bool sk_qkv = true, sk_down = true;
-  // those shapes at 161-288 rows in one tile of 18 token blocks per k slice
-  // (GVC_SK_TALL=0: two tiles of 10, testing)
+  // the other sessions' gate/up, QKV and down projections on split-k launches
+  // (GVC_SK=0, GVC_SK_QKV=0, GVC_SK_DOWN=0: the per-pair kernel, at every
+  // row count; testing)
+  bool sk_gemm = true, sk_qkv = true, sk_down = true;
+  // those and the output projection on the tile kernel where tile_gemm_wanted
+  // says so, and the down projection in tall tiles (GVC_SK_TALL=0: split-k in
+  // tiles of 10 token blocks and the per-pair kernel only; testing)
   bool sk_tall = true;
-  // the output projection on the narrow split-k shape where tall tiles apply
-  // (GVC_SK_O=0: the per-pair kernel at every height)
-  bool sk_o = true;
+  // GVC_SK_CORE=0: what split-k would run goes to the tile kernel (testing)
+  bool tile_always = false;
   // persistent decode pass (k_decode.hip): eligible shape, its grid and LDS
   bool persist = false;
   int persist_wg = 0;
@@ -410,21 +402,33 @@ GemmArgs base_args(const gvc_ctx* c) {
 }
 
 
-// Split-k launch of a prompt-pass projection (k_gemm_sk + slice sum and
-// epilogue); the slices depend only on the matrix shape.
-int32_t run_gemm_sk(gvc_ctx* c, GemmArgs& a, int epi, int M, int cls, int slices, int shape = SK_GU) {
+// A prompt-pass projection of a split-k session: split-k launches (shape
+// SK_WIDE or SK_NARROW), or the tile kernel adding up the same slices, which
+// depend only on the matrix shape.  shape 0: the per-pair kernel, whose k
+// shares are the slices, or the tile kernel.
+int32_t run_gemm(gvc_ctx* c, GemmArgs& a, int epi, int M, int cls, bool big = false);
+int32_t run_gemm_sliced(gvc_ctx* c, GemmArgs& a, int epi, int M, int cls, int slices, int shape) {
   if (M <= 0) return GVC_OK;
   const Plan& p = c->p;
+  if (shape == 0) tile_gemm(a, M, c->force_splits);
+  if (slices == 0) slices = a.splits;
   a.M = M;
   a.mblocks = (M + 15) / 16;
   const int kps = (a.KB + slices - 1) / slices;
+  if ((c->sk_tall && tile_gemm_wanted(a, epi)) || (c->tile_always && shape != 0)) {
+    a.sk_steps = kps;
+    a.tile_shape = c->tile_shape;
+    ProfScope ps(c, cls);
+    HIP_TRY(launch_gemm_tile(a, epi, c->stream));
+    return GVC_OK;
+  }
+  if (shape == 0) return run_gemm(c, a, epi, M, cls);
   a.sk_steps = kps;
   a.sk_slices = (a.KB + kps - 1) / kps;
   const int nblk = a.wblk[0] * (a.map == MAP_QKV ? 3 : (a.map == MAP_GU ? 2 : 1));
   const int gb = gemm_sk_group_blocks(shape);
   a.sk_groups = (nblk + gb - 1) / gb;
   a.part = c->K<float>(p.part_off);
-  a.sk_dx = c->sk_dx;
   a.sk_shape = shape;
   a.sk_tall = c->sk_tall ? 1 : 0;
   a.part_ld = nblk * 16;
@@ -435,14 +439,14 @@ int32_t run_gemm_sk(gvc_ctx* c, GemmArgs& a, int epi, int M, int cls, int slices
   return GVC_OK;
 }
 
-int32_t run_gemm(gvc_ctx* c, GemmArgs& a, int epi, int M, int cls, bool big = false) {
+int32_t run_gemm(gvc_ctx* c, GemmArgs& a, int epi, int M, int cls, bool big) {
   if (M <= 0) return GVC_OK;
   if (big) {
     a.M = M;
     a.mblocks = (M + 15) / 16;
-    a.big_tw = c->big_tw;
+    a.tile_shape = c->tile_shape;
     ProfScope ps(c, cls);
-    HIP_TRY(launch_gemm_big(a, epi, c->stream));
+    HIP_TRY(launch_gemm_tile(a, epi, c->stream));
     return GVC_OK;
   }
   tile_gemm(a, M, c->force_splits);
@@ -595,8 +599,8 @@ int32_t run_layer(gvc_ctx* c, int l, const RowMap& rows, int M, float* src, floa
     a.map = MAP_QKV; a.n_pairs = 3 * p.wq[l].Nblk / 2; a.n_out = p.d.d_model; a.KB = p.KBd;
     a.x = reinterpret_cast<const bf16x8*>(X);
     a.e.rows = rows; a.e.q = Q; a.e.kc = c->Kc(l); a.e.vc = c->Vc(l);
-    int32_t r = c->sk_qkv && c->sk_dx && !c->big_gemm ? run_gemm_sk(c, a, EPI_QKV, M, k0, kSkQkvSlices, SK_WIDE)
-                                                       : run_gemm(c, a, EPI_QKV, M, k0, c->big_gemm);
+    int32_t r = c->sk_qkv && !c->big_gemm ? run_gemm_sliced(c, a, EPI_QKV, M, k0, kSkQkvSlices, SK_WIDE)
+                                          : run_gemm(c, a, EPI_QKV, M, k0, c->big_gemm);
     if (r) return r;
   }
   {
@@ -617,10 +621,8 @@ int32_t run_layer(gvc_ctx* c, int l, const RowMap& rows, int M, float* src, floa
     a.map = MAP_PLAIN; a.n_pairs = (p.wo[l].Nblk + 1) / 2; a.n_out = p.d.d_model; a.KB = p.KBd;
     a.x = reinterpret_cast<const bf16x8*>(O);
     a.e.rows = rows; a.e.resid = src; a.e.resid_mapped = mapped; a.e.out = R; a.e.out_mapped = 0;
-    // 8 k slices: the per-pair kernel's 8 k shares, summed in the same order
-    const bool o_sk = c->sk_o && c->sk_tall && c->sk_dx && !c->big_gemm && gemm_sk_tall_rows(M);
-    int32_t r = o_sk ? run_gemm_sk(c, a, EPI_RESID, M, k0 + 2, kSkDownSlices, SK_NARROW)
-                     : run_gemm(c, a, EPI_RESID, M, k0 + 2, c->big_gemm);
+    int32_t r = c->big_gemm ? run_gemm(c, a, EPI_RESID, M, k0 + 2, true)
+                            : run_gemm_sliced(c, a, EPI_RESID, M, k0 + 2, 0, 0);
     if (r) return r;
   }
   {
@@ -635,7 +637,7 @@ int32_t run_layer(gvc_ctx* c, int l, const RowMap& rows, int M, float* src, floa
     a.map = MAP_GU; a.n_pairs = p.wg[l].Nblk; a.n_out = p.F; a.KB = p.KBd;
     a.x = reinterpret_cast<const bf16x8*>(X);
     a.e.rows = rows; a.e.act = A; a.e.kb_act = p.KBf; a.e.n_feat = p.F;
-    int32_t r = c->sk_gemm && !c->big_gemm ? run_gemm_sk(c, a, EPI_SILU, M, k0 + 3, kSkGuSlices, c->sk_dx ? SK_WIDE : SK_GU)
+    int32_t r = c->sk_gemm && !c->big_gemm ? run_gemm_sliced(c, a, EPI_SILU, M, k0 + 3, kSkGuSlices, SK_WIDE)
                                            : run_gemm(c, a, EPI_SILU, M, k0 + 3, c->big_gemm);
     if (r) return r;
   }
@@ -645,9 +647,8 @@ int32_t run_layer(gvc_ctx* c, int l, const RowMap& rows, int M, float* src, floa
     a.map = MAP_PLAIN; a.n_pairs = (p.wd[l].Nblk + 1) / 2; a.n_out = p.d.d_model; a.KB = p.KBf;
     a.x = reinterpret_cast<const bf16x8*>(A);
     a.e.rows = rows; a.e.resid = R; a.e.resid_mapped = 0; a.e.out = dst; a.e.out_mapped = mapped;
-    int32_t r = c->sk_down && c->sk_dx && !c->big_gemm
-                    ? run_gemm_sk(c, a, EPI_RESID, M, k0 + 4, kSkDownSlices, SK_NARROW)
-                    : run_gemm(c, a, EPI_RESID, M, k0 + 4, c->big_gemm);
+    int32_t r = c->sk_down && !c->big_gemm ? run_gemm_sliced(c, a, EPI_RESID, M, k0 + 4, kSkDownSlices, SK_NARROW)
+                                           : run_gemm(c, a, EPI_RESID, M, k0 + 4, c->big_gemm);
     if (r) return r;
   }
   return GVC_OK;
@@ -896,12 +897,11 @@ int32_t gvc_init_cache(const gvc_desc* desc, const gvc_weights* wt, void* weight
   if (const char* fs = getenv("GVC_FORCE_SPLITS")) c->force_splits = atoi(fs);
   c->big_gemm = p.B * p.P >= kBigRows;
   if (const char* sk = getenv("GVC_SK")) c->sk_gemm = atoi(sk) != 0;
-  if (const char* sc = getenv("GVC_SK_CORE")) c->sk_dx = atoi(sc) != 0;
+  if (const char* sc = getenv("GVC_SK_CORE")) c->tile_always = atoi(sc) == 0;
   if (const char* e = getenv("GVC_SK_QKV")) c->sk_qkv = atoi(e) != 0;
   if (const char* e = getenv("GVC_SK_DOWN")) c->sk_down = atoi(e) != 0;
   if (const char* e = getenv("GVC_SK_TALL")) c->sk_tall = atoi(e) != 0;
-  if (const char* e = getenv("GVC_SK_O")) c->sk_o = atoi(e) != 0;
-  if (const char* tw = getenv("GVC_BIG_TW")) c->big_tw = atoi(tw);
+  if (const char* tw = getenv("GVC_BIG_TW")) c->tile_shape = atoi(tw);
   if (const char* g = getenv("GVC_GEMM")) {
     if (!strcmp(g, "big")) c->big_gemm = true;
     if (!strcmp(g, "small")) c->big_gemm = false;

@@ -8,7 +8,7 @@ namespace gvc {
 // Work units of a GEMM launch.  Pair maps give a workgroup two 16-row weight
 // blocks whose epilogue partners share lanes; single maps give it one block.
 enum { MAP_PLAIN = 0, MAP_QKV = 1, MAP_GU = 2, MAP_SINGLE = 3, MAP_QKV_SINGLE = 4 };
-enum { SK_GU = 0, SK_WIDE = 1, SK_NARROW = 2 };
+enum { SK_WIDE = 1, SK_NARROW = 2 };
 enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SILU = 2, EPI_STORE = 3, EPI_EMBED = 4, EPI_QKV_RAW = 5, EPI_PATCH = 6,
        EPI_GELU = 7 };
 
@@ -66,20 +66,24 @@ struct GemmArgs {
   int tgroups;                // token groups per workgroup (KT)
   const bf16x8* x;      // frag-layout activations
   int M, mblocks, mtiles;
-  // split-k variant (k_gemm_sk + k_gemm_sk_epi): the k range in sk_slices
+  // split-k variant (k_gemm_dx + k_gemm_sk_epi): the k range in sk_slices
   // slices of sk_steps k steps, fp32 partial sums part[slice][row][feature]
   // with part_ld features per row (all matrices' blocks, matrix-major) and
-  // part_rows rows per slice; sk_groups weight-block groups per slice
+  // part_rows rows per slice; sk_groups weight-block groups per slice.  The
+  // tile kernel adds up slices of sk_steps itself (0: one sum).
   float* part;
   int sk_slices, sk_steps, sk_groups, part_ld, part_rows;
-  int big_tw;           // many-row kernel: token blocks per wave (2, 3 or 4), 0 = chosen per launch
-  int sk_dx;            // split-k core: 0 = k_gemm_sk, 1 = k_gemm_dx (decoupled weight and token streams)
-  int sk_shape;         // k_gemm_dx work split: SK_GU (8 waves x 2 blocks), SK_WIDE (12 x 1),
-                        // SK_NARROW (8 x 1); see gemm_sk_group_blocks()
-  int sk_tall;          // SK_WIDE / SK_NARROW at 11-18 token blocks: one tile of 18 blocks per
-                        // k slice instead of two of 10 (0 = always tiles of 10)
+  int tile_shape;       // tile kernel: 1 + index of the shape, 0 = chosen per launch (testing)
+  int sk_shape;         // k_gemm_dx work split: SK_WIDE (12 blocks) or SK_NARROW (8), see gemm_sk_group_blocks()
+  int sk_tall;          // SK_NARROW at 11-18 token blocks: one tile of 18 blocks per k slice instead
+                        // of two of 10 (0 = always tiles of 10)
   EpiArgs e;
 };
+
+// A residual projection of more k steps than this stays on split-k up to 288
+// rows (tile_gemm_wanted): the 7B output projection has 128, the down
+// projection 344.
+constexpr int kTileLongK = 192;
 
 // k-steps per pipelined register chunk for a tile of NT blocks of 16 token rows.
 constexpr int gemm_pf(int NT) { return NT == 1 ? 4 : (NT <= 3 ? 4 : (NT <= 6 ? 2 : 1)); }

@@ -36,14 +36,18 @@ hipError_t launch_gather_visual(const bf16* src, const int* idx, const int* pos,
 // keeps one choice.
 hipError_t launch_rmsnorm(const float* src, const int* idx, int M, int d, const float* gain, float eps,
                           bf16* x, int KB, bool tiled, hipStream_t s);
-hipError_t launch_gemm_big(const GemmArgs& a, int epi, hipStream_t s);
-// Split-k prompt-pass GEMM (k_gemm_sk or k_gemm_dx, then the slice sum and
-// epilogue); workgroups own groups of gemm_sk_group_blocks(a.sk_shape)
-// weight blocks.
+// Tiled GEMM (k_tile.hip): EPI_QKV, EPI_RESID, EPI_SILU, EPI_EMBED; with
+// a.sk_steps > 0 summed in slices of that many k steps.
+hipError_t launch_gemm_tile(const GemmArgs& a, int epi, hipStream_t s);
+// Whether a projection of a split-k session (a.M, a.mblocks, a.n_pairs, a.KB)
+// takes the tile kernel, in slices, instead of split-k.
+bool tile_gemm_wanted(const GemmArgs& a, int epi);
+// Split-k prompt-pass GEMM (k_gemm_dx, then the slice sum and epilogue);
+// workgroups own groups of gemm_sk_group_blocks(a.sk_shape) weight blocks.
 hipError_t launch_gemm_sk(const GemmArgs& a, int epi, hipStream_t s);
 int gemm_sk_group_blocks(int sk_shape);
-// Whether a split-k launch of M rows takes one tall tile per k slice (the
-// wide and narrow shapes at 161-288 rows).
+// Whether a narrow split-k launch of M rows takes one tall tile per k slice
+// (161-288 rows).
 bool gemm_sk_tall_rows(int M);
 hipError_t launch_gemm(const GemmArgs& a, int epi, int NT, hipStream_t s);
 // Stage 2 signal of one layer: tv[b * tv_bstride + h * N + n] = sum over the

@@ -1,0 +1,286 @@
+// Tiled GEMM of the prompt pass for launches that fill the chip with whole
+// tiles: every projection of the many-row sessions, and QKV, gate/up, output
+// and down projections of the others from the row counts given at
+// tile_gemm_wanted() on.
+//
+// A workgroup of WW x WT waves owns WW * WP weight pairs x WT * TB blocks of
+// 16 token rows and walks the whole k range in order.  Every k step, both
+// operands' fragments of the tile are copied straight into LDS
+// (global_load_lds), S stages deep; wave (ww, wt) holds the fragments of step
+// k in registers and multiplies them while those of step k + 1 are read from
+// LDS, the reads spread between the MFMAs.  What bounds it is LDS: a wave tile
+// of 2 WP x TB blocks reads 2 WP + TB fragments per 2 WP * TB MFMAs, so
+// with the reads in front of the MFMAs (one register set, the kernel before
+// this one) the two took turns.  7B projections alone, reads in front -> beside
+// (best shape each): 2368 rows QKV 287 -> 234 us, output 94 -> 79, down 242 ->
+// 191; 736 rows 98 -> 77, 45 -> 35, gate/up 148 -> 135, down 143 -> 87.
+// Against split-k with fp32 partial sums and a kernel that adds them: 589 rows
+// QKV 147 -> 59 us, output 76 -> 32, gate/up 214 -> 118, down 121 -> 82; 282
+// rows QKV 56 -> 47, output 34 -> 29, gate/up 89 -> 60.
+//
+// A row's sum runs over k in order, so it does not depend on the tile.  With
+// SL the sum is cut into the split-k launches' slices: a slice is summed from
+// zero and added to the total, which gives bit for bit what those launches
+// and k_gemm_ks (its k shares) give, so a session may choose by row count.
+#include <algorithm>
+#include <atomic>
+
+#include "gvc_epilogue.h"
+
+namespace gvc {
+
+template <int EPI, int WP, int TB, int WW, int WT, int S, int OCC, bool SL>
+__global__ __launch_bounds__(WW * WT * 64, OCC) void k_gemm_tile(const GemmArgs a, int mtiles, int ntiles) {
+  constexpr int NW = WW * WT, WF = 2 * WW * WP, TF = WT * TB, FR = WF + TF;
+  constexpr int LPW = (FR + NW - 1) / NW;   // fragment copies per wave per k step
+  static_assert(S >= 3 && (S - 2) * LPW < 64, "vmcnt range");
+  extern __shared__ u32x4b tile_lds[];      // [S][FR][64]
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ww = wv % WW, wt = wv / WW;
+  // XCD-aware order: all tiles of one weight tile run on XCD (tile % 8) and
+  // share its weights in that L2; within an XCD, jobs run in groups of 8
+  // token tiles x all of the XCD's weight tiles, so the workgroups resident
+  // at one time share both operands' tiles
+  const int x = blockIdx.x, xcd = x & 7, i = x >> 3;
+  const int nnt = (ntiles + 7) / 8, g = i / (8 * nnt), r = i % (8 * nnt);
+  const int gs = min(8, mtiles - g * 8);
+  const int nt = xcd + 8 * (r / gs), mt = g * 8 + r % gs;
+  if (nt >= ntiles) return;
+  const int pair0 = nt * WW * WP, tb0 = mt * TF, KB = a.KB;
+  const bf16x8* src[LPW];
+  int dst[LPW];
+#pragma unroll
+  for (int l = 0; l < LPW; ++l) {
+    const int f = min(wv + l * NW, FR - 1);
+    dst[l] = f;
+    if (f < WF) {
+      int ma, ba, mb, bb; bool ok;
+      map_pair(a, min(pair0 + f / 2, a.n_pairs - 1), ma, ba, mb, bb, ok);
+      src[l] = ((f & 1) ? a.w[mb] + (size_t)bb * KB * 64 : a.w[ma] + (size_t)ba * KB * 64) + lane;
+    } else {
+      src[l] = a.x + (size_t)min(tb0 + f - WF, a.mblocks - 1) * KB * 64 + lane;
+    }
+  }
+  int fill = 0, fill_k = 0, rd_stage = 0;   // next stage to fill and its k step; next stage to read
+  auto issue = [&]() __attribute__((always_inline)) {   // k steps past the end re-read the last one (in bounds)
+    u32x4b* st = tile_lds + fill * FR * 64;
+    const size_t o = (size_t)min(fill_k, KB - 1) * 64;
+#pragma unroll
+    for (int l = 0; l < LPW; ++l) __builtin_amdgcn_global_load_lds(GPB(src[l] + o), LPB(st + dst[l] * 64), 16, 0, 0);
+    ++fill_k;
+    fill = fill + 1 == S ? 0 : fill + 1;
+  };
+  floatx4 acc[2 * WP][TB], tot[SL ? 2 * WP : 1][SL ? TB : 1];
+#pragma unroll
+  for (int p = 0; p < 2 * WP; ++p)
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+      acc[p][j] = floatx4{0, 0, 0, 0};
+      if constexpr (SL) tot[p][j] = floatx4{0, 0, 0, 0};
+    }
+  typedef bf16x8 WFrag[2 * WP];
+  typedef bf16x8 XFrag[TB];
+  auto read = [&](WFrag& w, XFrag& t) __attribute__((always_inline)) {
+    const u32x4b* st = tile_lds + rd_stage * FR * 64;
+#pragma unroll
+    for (int j = 0; j < TB; ++j) t[j] = __builtin_bit_cast(bf16x8, st[(WF + wt * TB + j) * 64 + lane]);
+#pragma unroll
+    for (int p = 0; p < 2 * WP; ++p) w[p] = __builtin_bit_cast(bf16x8, st[(2 * ww * WP + p) * 64 + lane]);
+    rd_stage = rd_stage + 1 == S ? 0 : rd_stage + 1;
+  };
+  auto multiply = [&](const WFrag& w, const XFrag& t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int p = 0; p < 2 * WP; ++p)
+#pragma unroll
+      for (int j = 0; j < TB; ++j) acc[p][j] = mfma16(w[p], t[j], acc[p][j]);
+  };
+  int slice_end = SL ? a.sk_steps : 0;
+  auto end_slice = [&](int k) __attribute__((always_inline)) {   // after the k-th step (from 1)
+    if (!SL || (k != slice_end && k != KB)) return;
+    slice_end += a.sk_steps;
+    if constexpr (SL)
+#pragma unroll
+      for (int p = 0; p < 2 * WP; ++p)
+#pragma unroll
+        for (int j = 0; j < TB; ++j) {
+          tot[p][j] += acc[p][j];
+          acc[p][j] = floatx4{0, 0, 0, 0};
+        }
+  };
+#pragma unroll
+  for (int c = 0; c < S - 1; ++c) issue();
+  wait_vmcnt<(S - 2) * LPW>();
+  lds_barrier();
+  WFrag wa, wb;
+  XFrag xa, xb;
+  read(wa, xa);
+  // Step k: w0, x0 hold its fragments; those of step k + 1 are read beside its
+  // MFMAs.  The stage filled here last held step k - 1, whose reads every
+  // wave had finished before its MFMAs, so before this barrier.
+  auto step = [&](const WFrag& w0, const XFrag& x0, WFrag& w1, XFrag& x1) __attribute__((always_inline)) {
+    wait_vmcnt<(S - 3) * LPW>();
+    lds_barrier();
+    issue();
+    read(w1, x1);
+    multiply(w0, x0);
+    constexpr int NR = 2 * WP + TB, NM = 2 * WP * TB;
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);         // an LDS read,
+      __builtin_amdgcn_sched_group_barrier(0x008, NM / NR, 0);   // then its share of the MFMAs
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, NM - NM / NR * NR, 0);
+  };
+  int k = 0;
+  for (; k + 2 <= KB; k += 2) {
+    step(wa, xa, wb, xb);
+    end_slice(k + 1);
+    step(wb, xb, wa, xa);
+    end_slice(k + 2);
+  }
+  if (k < KB) {
+    multiply(wa, xa);
+    end_slice(KB);
+  }
+  wait_vmcnt<0>();   // direct-to-LDS loads must land before the workgroup ends
+  const int col = lane & 15;
+#pragma unroll
+  for (int p = 0; p < WP; ++p) {
+    const int pair = pair0 + ww * WP + p;
+    if (pair >= a.n_pairs) continue;
+    int ma, ba, mb, bb; bool b_ok;
+    map_pair(a, pair, ma, ba, mb, bb, b_ok);
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+      const int m = (tb0 + wt * TB + j) * 16 + col;
+      if constexpr (SL)
+        epilogue<EPI>(a, pair, lane, min(m, a.M - 1), tot[2 * p][j], tot[2 * p + 1][j], b_ok, m < a.M, 1.0f);
+      else
+        epilogue<EPI>(a, pair, lane, min(m, a.M - 1), acc[2 * p][j], acc[2 * p + 1][j], b_ok, m < a.M, 1.0f);
+    }
+  }
+}
+
+// Shapes: weight blocks x token blocks of a workgroup's tile, workgroups per
+// CU, and what a k step takes (ns) with one and with all of them resident,
+// measured on the 7B projections at 148-2368 rows with most CUs busy.
+struct TileShape {
+  int wblk, tblk, occ;
+  float one, all;
+};
+constexpr TileShape kTiles[] = {
+    {6, 10, 1, 290, 290},  {4, 10, 2, 234, 414},  {12, 10, 1, 385, 385}, {8, 6, 2, 246, 430},
+    {12, 12, 1, 480, 480}, {16, 10, 1, 550, 550}, {16, 16, 1, 820, 820}, {8, 10, 2, 370, 594},
+};
+constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+constexpr int kSlicedTiles = 5;   // the first ones also have an SL form (its totals fit the registers)
+
+static int tile_count(const GemmArgs& a, const TileShape& t) {
+  return (2 * a.n_pairs + t.wblk - 1) / t.wblk * ((a.mblocks + t.tblk - 1) / t.tblk);
+}
+
+// Time of a launch in ns: whole rounds of resident workgroups, then the rest,
+// at the measured step times, plus launch and epilogue.
+static float tile_time(const GemmArgs& a, const TileShape& t, int cus) {
+  const int n = tile_count(a, t), full = n / (t.occ * cus), rem = n % (t.occ * cus);
+  const float steps = full * t.all + (rem == 0 ? 0.f : (rem > cus ? t.all : t.one));
+  return a.KB * steps + 10000.f + 4000.f * (full + (rem > 0) - 1);
+}
+
+static hipError_t device_cus(int& cus) {
+  static std::atomic<int> known{0};
+  cus = known.load(std::memory_order_relaxed);
+  if (cus > 0) return hipSuccess;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  if (cus <= 0) return hipErrorInvalidDevice;
+  known.store(cus, std::memory_order_relaxed);
+  return hipSuccess;
+}
+
+template <int EPI, int WP, int TB, int WW, int WT, int S, int OCC, bool SL>
+static hipError_t launch_tile_one(const GemmArgs& a, hipStream_t s) {
+  constexpr int lds = S * (2 * WW * WP + WT * TB) * 1024;
+  static_assert(lds <= 160 * 1024, "LDS");
+  static std::atomic<bool> attr{false};
+  if (!attr.load(std::memory_order_acquire)) {
+    const hipError_t e =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_tile<EPI, WP, TB, WW, WT, S, OCC, SL>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    attr.store(true, std::memory_order_release);
+  }
+  const int mtiles = (a.mblocks + WT * TB - 1) / (WT * TB), ntiles = (a.n_pairs + WW * WP - 1) / (WW * WP);
+  hipLaunchKernelGGL((k_gemm_tile<EPI, WP, TB, WW, WT, S, OCC, SL>), dim3(8 * ((ntiles + 7) / 8) * mtiles),
+                     dim3(WW * WT * 64), lds, s, a, mtiles, ntiles);
+  return hipGetLastError();
+}
+
+template <int EPI, bool SL>
+static hipError_t launch_tile_shape(const GemmArgs& a, int shape, hipStream_t s) {
+  switch (shape) {   // as in kTiles
+    case 0: return launch_tile_one<EPI, 1, 5, 3, 2, 8, 1, SL>(a, s);
+    case 1: return launch_tile_one<EPI, 1, 5, 2, 2, 5, 2, SL>(a, s);
+    case 2: return launch_tile_one<EPI, 1, 5, 6, 2, 7, 2, SL>(a, s);
+    case 3: return launch_tile_one<EPI, 2, 3, 2, 2, 5, 2, SL>(a, s);
+    case 4: return launch_tile_one<EPI, 3, 3, 2, 4, 6, 2, SL>(a, s);
+    default: break;
+  }
+  if constexpr (!SL) {
+    switch (shape) {
+      case 5: return launch_tile_one<EPI, 2, 5, 4, 2, 5, 2, SL>(a, s);
+      case 6: return launch_tile_one<EPI, 4, 4, 2, 4, 5, 2, SL>(a, s);
+      case 7: return launch_tile_one<EPI, 2, 5, 2, 2, 4, 2, SL>(a, s);
+      default: break;
+    }
+  }
+  return hipErrorInvalidValue;
+}
+
+// The shape that tile_time puts first.
+static int best_tile(const GemmArgs& a, int n_shapes, int cus) {
+  int best = 0;
+  for (int i = 1; i < n_shapes; ++i)
+    if (tile_time(a, kTiles[i], cus) < tile_time(a, kTiles[best], cus)) best = i;
+  return best;
+}
+
+hipError_t launch_gemm_tile(const GemmArgs& a, int epi, hipStream_t s) {
+  if (a.map == MAP_SINGLE || a.map == MAP_QKV_SINGLE || a.e.ssq_in) return hipErrorInvalidValue;
+  int cus = 0;
+  const hipError_t e = device_cus(cus);
+  if (e != hipSuccess) return e;
+  const bool sl = a.sk_steps > 0;
+  const int n = sl ? kSlicedTiles : kNumTiles;
+  const int shape = a.tile_shape >= 1 && a.tile_shape <= n ? a.tile_shape - 1 : best_tile(a, n, cus);
+  switch (epi) {
+    case EPI_QKV: return sl ? launch_tile_shape<EPI_QKV, true>(a, shape, s) : launch_tile_shape<EPI_QKV, false>(a, shape, s);
+    case EPI_RESID:
+      return sl ? launch_tile_shape<EPI_RESID, true>(a, shape, s) : launch_tile_shape<EPI_RESID, false>(a, shape, s);
+    case EPI_SILU:
+      return sl ? launch_tile_shape<EPI_SILU, true>(a, shape, s) : launch_tile_shape<EPI_SILU, false>(a, shape, s);
+    case EPI_EMBED: return sl ? hipErrorInvalidValue : launch_tile_shape<EPI_EMBED, false>(a, shape, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// Whether a split-k session's launch goes to the tile kernel.  Above 160 rows
+// a split-k launch takes several token tiles that each stream the weights, so
+// always there, except the down projection up to 288 rows, whose one 18-block
+// tile per k slice is ahead (282 rows: 46 us against 80; its 344 k steps are
+// a long walk for one workgroup).  Up to 160 rows only where one round of
+// tiles takes at least three quarters of the compute units (7B gate/up at 148
+// rows: 48 us against 53; QKV 40 against 40).
+bool tile_gemm_wanted(const GemmArgs& a, int epi) {
+  if (epi == EPI_RESID && a.KB > kTileLongK) return a.mblocks > 18;
+  if (a.mblocks > 10) return true;
+  if (epi != EPI_SILU) return false;
+  int cus = 0;
+  if (device_cus(cus) != hipSuccess) return false;
+  const int n = tile_count(a, kTiles[best_tile(a, kSlicedTiles, cus)]);
+  return 4 * n >= 3 * cus && n <= cus;
+}
+
+}  // namespace gvc
