@@ -48,6 +48,11 @@ __device__ __forceinline__ void add_bias(floatx4& v, const float* bias, int f) {
   v[0] += b.x; v[1] += b.y; v[2] += b.z; v[3] += b.w;
 }
 
+// RoPE of the pair (a, b) of dims i and i + d_h/2.  The fused multiply-adds are
+// written out: left to the compiler, two kernels could round differently.
+__device__ __forceinline__ float rope_lo(float a, float b, float c, float s) { return __builtin_fmaf(a, c, -(b * s)); }
+__device__ __forceinline__ float rope_hi(float a, float b, float c, float s) { return __builtin_fmaf(b, c, a * s); }
+
 // Epilogue of one lane: 4 consecutive output features of block A and of
 // block B for token row m.  Every lane of the wave calls it (some epilogues
 // shuffle across lanes); `valid` says whether row m exists (m is already
@@ -79,8 +84,8 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, int pair, int lane, 
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float2 c = cs[i];
-        ra[i] = va[i] * c.x - vb[i] * c.y;
-        rb[i] = vb[i] * c.x + va[i] * c.y;
+        ra[i] = rope_lo(va[i], vb[i], c.x, c.y);
+        rb[i] = rope_hi(va[i], vb[i], c.x, c.y);
       }
     } else {
 #pragma unroll

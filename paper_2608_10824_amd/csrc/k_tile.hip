@@ -15,8 +15,9 @@
 // (best shape each): 2368 rows QKV 287 -> 234 us, output 94 -> 79, down 242 ->
 // 191; 736 rows 98 -> 77, 45 -> 35, gate/up 148 -> 135, down 143 -> 87.
 // Against split-k with fp32 partial sums and a kernel that adds them: 589 rows
-// QKV 147 -> 59 us, output 76 -> 32, gate/up 214 -> 118, down 121 -> 82; 282
-// rows QKV 56 -> 47, output 34 -> 29, gate/up 89 -> 60.
+// QKV 147 -> 72 us, output 76 -> 32, gate/up 214 -> 123, down 121 -> 82; 282
+// rows QKV 56 -> 47, output 34 -> 29, gate/up 89 -> 60.  Ten shapes, because
+// whole rounds of workgroups on 256 CUs leave a rest that depends on the sizes.
 //
 // A row's sum runs over k in order, so it does not depend on the tile.  With
 // SL the sum is cut into the split-k launches' slices: a slice is summed from
@@ -28,6 +29,126 @@
 #include "gvc_epilogue.h"
 
 namespace gvc {
+
+// Epilogue of one wave: accumulators v of WP pairs (from pair0) x TB token
+// blocks (from tb0).  The fused epilogue of one (pair, block) loads its row's
+// numbers, then what they point to (RoPE, residual), then stores; one after
+// the other that chain cost a 7B QKV launch of 2368 rows 20 us per round of
+// tiles.  For QKV and the residual the row numbers of all blocks are loaded
+// first, and a block's operands while the block before it is stored.
+template <int EPI, int WP, int TB>
+__device__ __forceinline__ void tile_epilogue(const GemmArgs& a, int pair0, int lane, int tb0,
+                                              const floatx4 (&v)[2 * WP][TB]) {
+  const EpiArgs& e = a.e;
+  const int col = lane & 15, sub = (lane >> 4) * 4;
+  auto row = [&](int j) { return (tb0 + j) * 16 + col; };
+  if constexpr (EPI == EPI_QKV) {
+    if (!e.bias[0] && e.rope) {
+      const int dh = e.head_dim, half = dh >> 1;
+      int pos[TB], ep[TB];
+#pragma unroll
+      for (int j = 0; j < TB; ++j) {
+        const int m = min(row(j), a.M - 1);
+        pos[j] = e.rows.pos[m];
+        ep[j] = e.rows.ep[m];
+      }
+      int mat[WP], head[WP], ia[WP];
+#pragma unroll
+      for (int p = 0; p < WP; ++p) {
+        int mb, bb, ba; bool ok;
+        map_pair(a, min(pair0 + p, a.n_pairs - 1), mat[p], ba, mb, bb, ok);
+        head[p] = ba / (dh >> 4);
+        ia[p] = (ba % (dh >> 4)) * 16 + sub;   // dim within head, < half
+      }
+      float4 cs[2][WP][2];   // (cos, sin) of 4 dims
+      auto load = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < WP; ++p) {
+          const float4* r = (const float4*)(e.rope + (size_t)pos[j] * half + ia[p]);
+          cs[j & 1][p][0] = r[0];
+          cs[j & 1][p][1] = r[1];
+        }
+      };
+      load(0);
+#pragma unroll
+      for (int j = 0; j < TB; ++j) {
+        if (j + 1 < TB) load(j + 1);
+        const int m = row(j);
+#pragma unroll
+        for (int p = 0; p < WP; ++p) {
+          if (pair0 + p >= a.n_pairs || m >= a.M) continue;
+          const floatx4 va = v[2 * p][j], vb = v[2 * p + 1][j];
+          if (mat[p] < 2) {
+            const float4 c0 = cs[j & 1][p][0], c1 = cs[j & 1][p][1];
+            const float c[4] = {c0.x, c0.z, c1.x, c1.z}, s[4] = {c0.y, c0.w, c1.y, c1.w};
+            u16x4 oa, ob;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              oa[i] = f2bf(rope_lo(va[i], vb[i], c[i], s[i]));
+              ob[i] = f2bf(rope_hi(va[i], vb[i], c[i], s[i]));
+            }
+            bf16* o = mat[p] == 0 ? e.q + (size_t)m * e.d + head[p] * dh
+                                  : e.kc + ((size_t)(ep[j] * e.n_heads + head[p]) * e.kv_pad + pos[j]) * dh;
+            *(u16x4*)(o + ia[p]) = oa;
+            *(u16x4*)(o + ia[p] + half) = ob;
+          } else {
+            bf16* o = e.vc + (size_t)(ep[j] * e.n_heads + head[p]) * dh * e.kv_pad + pos[j];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              o[(size_t)(ia[p] + i) * e.kv_pad] = f2bf(va[i]);
+              o[(size_t)(ia[p] + half + i) * e.kv_pad] = f2bf(vb[i]);
+            }
+          }
+        }
+      }
+      return;
+    }
+  }
+  if constexpr (EPI == EPI_RESID) {
+    if (!e.bias[0] && !e.xn && a.map == MAP_PLAIN) {
+      size_t ri[TB], oi[TB];
+#pragma unroll
+      for (int j = 0; j < TB; ++j) {
+        const int m = min(row(j), a.M - 1), x = e.resid_mapped || e.out_mapped ? e.rows.idx[m] : m;
+        ri[j] = (size_t)(e.resid_mapped ? x : m) * e.d;
+        oi[j] = (size_t)(e.out_mapped ? x : m) * e.d;
+      }
+      const int last = 16 * a.wblk[0] - 4;   // blocks past the matrix re-read its last features
+      float4 r[2][2 * WP];
+      auto load = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 2 * WP; ++q)
+          r[j & 1][q] = *(const float4*)(e.resid + ri[j] + min((2 * pair0 + q) * 16 + sub, last));
+      };
+      load(0);
+#pragma unroll
+      for (int j = 0; j < TB; ++j) {
+        if (j + 1 < TB) load(j + 1);
+        if (row(j) >= a.M) continue;
+#pragma unroll
+        for (int q = 0; q < 2 * WP; ++q) {
+          const float4 x = r[j & 1][q];
+          const floatx4& y = v[q][j];
+          if (2 * pair0 + q < a.wblk[0])
+            *(float4*)(e.out + oi[j] + (2 * pair0 + q) * 16 + sub) =
+                float4{x.x + y[0], x.y + y[1], x.z + y[2], x.w + y[3]};
+        }
+      }
+      return;
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < WP; ++p) {
+    if (pair0 + p >= a.n_pairs) continue;
+    int ma, ba, mb, bb; bool b_ok;
+    map_pair(a, pair0 + p, ma, ba, mb, bb, b_ok);
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+      const int m = row(j);
+      epilogue<EPI>(a, pair0 + p, lane, min(m, a.M - 1), v[2 * p][j], v[2 * p + 1][j], b_ok, m < a.M, 1.0f);
+    }
+  }
+}
 
 template <int EPI, int WP, int TB, int WW, int WT, int S, int OCC, bool SL>
 __global__ __launch_bounds__(WW * WT * 64, OCC) void k_gemm_tile(const GemmArgs a, int mtiles, int ntiles) {
@@ -143,22 +264,10 @@ __global__ __launch_bounds__(WW * WT * 64, OCC) void k_gemm_tile(const GemmArgs 
     end_slice(KB);
   }
   wait_vmcnt<0>();   // direct-to-LDS loads must land before the workgroup ends
-  const int col = lane & 15;
-#pragma unroll
-  for (int p = 0; p < WP; ++p) {
-    const int pair = pair0 + ww * WP + p;
-    if (pair >= a.n_pairs) continue;
-    int ma, ba, mb, bb; bool b_ok;
-    map_pair(a, pair, ma, ba, mb, bb, b_ok);
-#pragma unroll
-    for (int j = 0; j < TB; ++j) {
-      const int m = (tb0 + wt * TB + j) * 16 + col;
-      if constexpr (SL)
-        epilogue<EPI>(a, pair, lane, min(m, a.M - 1), tot[2 * p][j], tot[2 * p + 1][j], b_ok, m < a.M, 1.0f);
-      else
-        epilogue<EPI>(a, pair, lane, min(m, a.M - 1), acc[2 * p][j], acc[2 * p + 1][j], b_ok, m < a.M, 1.0f);
-    }
-  }
+  if constexpr (SL)
+    tile_epilogue<EPI, WP, TB>(a, pair0 + ww * WP, lane, tb0 + wt * TB, tot);
+  else
+    tile_epilogue<EPI, WP, TB>(a, pair0 + ww * WP, lane, tb0 + wt * TB, acc);
 }
 
 // Shapes: weight blocks x token blocks of a workgroup's tile, workgroups per
@@ -169,8 +278,8 @@ struct TileShape {
   float one, all;
 };
 constexpr TileShape kTiles[] = {
-    {6, 10, 1, 290, 290},  {4, 10, 2, 234, 414},  {12, 10, 1, 385, 385}, {8, 6, 2, 246, 430},
-    {12, 12, 1, 480, 480}, {16, 10, 1, 550, 550}, {16, 16, 1, 820, 820}, {8, 10, 2, 370, 594},
+    {6, 10, 1, 300, 300},  {4, 10, 2, 234, 370},  {12, 10, 1, 425, 435}, {8, 6, 2, 246, 390},  {12, 12, 1, 480, 510},
+    {16, 10, 1, 520, 520}, {16, 16, 1, 740, 740}, {8, 10, 2, 370, 540},  {16, 14, 1, 680, 680}, {16, 12, 1, 600, 600},
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 constexpr int kSlicedTiles = 5;   // the first ones also have an SL form (its totals fit the registers)
@@ -233,6 +342,8 @@ static hipError_t launch_tile_shape(const GemmArgs& a, int shape, hipStream_t s)
       case 5: return launch_tile_one<EPI, 2, 5, 4, 2, 5, 2, SL>(a, s);
       case 6: return launch_tile_one<EPI, 4, 4, 2, 4, 5, 2, SL>(a, s);
       case 7: return launch_tile_one<EPI, 2, 5, 2, 2, 4, 2, SL>(a, s);
+      case 8: return launch_tile_one<EPI, 2, 7, 4, 2, 5, 2, SL>(a, s);
+      case 9: return launch_tile_one<EPI, 2, 6, 4, 2, 5, 2, SL>(a, s);
       default: break;
     }
   }
@@ -270,17 +381,10 @@ hipError_t launch_gemm_tile(const GemmArgs& a, int epi, hipStream_t s) {
 // a split-k launch takes several token tiles that each stream the weights, so
 // always there, except the down projection up to 288 rows, whose one 18-block
 // tile per k slice is ahead (282 rows: 46 us against 80; its 344 k steps are
-// a long walk for one workgroup).  Up to 160 rows only where one round of
-// tiles takes at least three quarters of the compute units (7B gate/up at 148
-// rows: 48 us against 53; QKV 40 against 40).
+// a long walk for one workgroup).  Up to 160 rows split-k is level or ahead
+// (7B gate/up at 148 rows: 48 us in a prompt pass against 52; QKV 40 and 40).
 bool tile_gemm_wanted(const GemmArgs& a, int epi) {
-  if (epi == EPI_RESID && a.KB > kTileLongK) return a.mblocks > 18;
-  if (a.mblocks > 10) return true;
-  if (epi != EPI_SILU) return false;
-  int cus = 0;
-  if (device_cus(cus) != hipSuccess) return false;
-  const int n = tile_count(a, kTiles[best_tile(a, kSlicedTiles, cus)]);
-  return 4 * n >= 3 * cus && n <= cus;
+  return a.mblocks > (epi == EPI_RESID && a.KB > kTileLongK ? 18 : 10);
 }
 
 }  // namespace gvc
