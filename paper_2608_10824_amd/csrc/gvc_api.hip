@@ -83,7 +83,7 @@ struct Plan {
   // workspace
   size_t rows_off, counts_off, epc_off, epo_off, stats_off, score_off, x_off, q_off, o_off, r_off, act_off, xdec_off, xf_off,
       ssq_a_off, ssq_f_off, qraw_off, kraw_off, part_off, part_bytes,
-      logits_off, rope_off, decrows_off, headrows_off, tokens_off, gate_m_off, gate_f_off, qkv3_off, bar_off,
+      logits_off, rope_off, decrows_off, headrows_off, tokens_off, qkv3_off, bar_off,
       hpart_off, ws_bytes;
 };
 
@@ -246,8 +246,6 @@ int32_t make_plan(const gvc_desc* dsc, Plan& p) {
   p.decrows_off = k.take((size_t)p.D * 3 * p.B * 4);
   p.headrows_off = k.take((size_t)3 * p.B * p.head_rows * 4);
   p.tokens_off = k.take((size_t)p.B * p.D * 4);
-  p.gate_m_off = k.take((size_t)p.B * 4);
-  p.gate_f_off = k.take((size_t)p.B * 4);
   p.qkv3_off = k.take((size_t)3 * p.B * d.d_model * 4);
   p.bar_off = k.take((size_t)kDecodeBarWords * 4);
   p.hpart_off = k.take((size_t)kDecodeMaxGrid * 8 * 4);
@@ -315,7 +313,11 @@ struct gvc_ctx {
   DecodeArgs dargs{};
   bool persist_ran = false;       // a launch sequence ran since the last check of the abort word
   bool tv_ready = false;          // a prompt pass has written the Stage 2 / Stage 3 signals
-  uint32_t abort_word = 0;        // host copy, read by margin_gate
+  HostBox* box = nullptr;         // pinned host memory (host address) and where the kernels see it
+  HostBox* box_dev = nullptr;
+  ~gvc_ctx() {
+    if (box) (void)hipHostFree(box);
+  }
   // launch timing of one kernel class (gvc_profile_begin / _end)
   int prof_cls = -1;
   std::vector<hipEvent_t> prof_ev;
@@ -894,6 +896,8 @@ int32_t gvc_init_cache(const gvc_desc* desc, const gvc_weights* wt, void* weight
   } while (0)
 
   INIT_TRY(hipGetDevice(&c->device));
+  INIT_TRY(hipHostMalloc(reinterpret_cast<void**>(&c->box), sizeof(HostBox), hipHostMallocMapped));
+  INIT_TRY(hipHostGetDevicePointer(reinterpret_cast<void**>(&c->box_dev), c->box, 0));
   if (const char* fs = getenv("GVC_FORCE_SPLITS")) c->force_splits = atoi(fs);
   c->big_gemm = p.B * p.P >= kBigRows;
   if (const char* sk = getenv("GVC_SK")) c->sk_gemm = atoi(sk) != 0;
@@ -1124,11 +1128,10 @@ int32_t gvc_step_prefill(gvc_ctx* c, const uint8_t* frame_t, const int32_t* text
   int* counts = c->K<int>(p.counts_off);
   int* epc = c->K<int>(p.epc_off);
   int* epo = c->K<int>(p.epo_off);
-  HIP_TRY(launch_build_rows(reuse_mask, c->S<int>(p.valid_off), p.B, p.L, p.N, p.P, c->K<int>(p.rows_off), counts, epc,
-                            epo, s));
-  HIP_TRY(hipMemcpyAsync(c->S<int>(p.rowcount_off), counts, (size_t)p.L * 4, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(c->counts.data(), counts, (size_t)p.L * 4, hipMemcpyDeviceToHost, s));
+  HIP_TRY(launch_build_rows(reuse_mask, c->S<int>(p.valid_off), p.B, p.L, p.N, p.P, c->K<int>(p.rows_off), counts,
+                            c->S<int>(p.rowcount_off), c->box_dev, epc, epo, s));
   HIP_TRY(hipStreamSynchronize(s));
+  c->counts.assign(c->box->counts, c->box->counts + p.L);
   for (int l = 0; l < p.L; ++l)
     if (c->counts[l] < 1 || c->counts[l] > p.B * p.P) return fail(GVC_EDEVICE, "corrupt row count");
   if (c->validate) {
@@ -1265,8 +1268,7 @@ int32_t gvc_decode_actions(gvc_ctx* c, int32_t* tokens_out, float* margins_out, 
                                  (size_t)p.V * 4, p.B, hipMemcpyDeviceToDevice, s));
     }
   }
-  HIP_TRY(hipMemcpyAsync(tokens_out, tok, (size_t)p.B * p.D * 4, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(margins_out, mg, (size_t)p.B * p.D * 4, hipMemcpyDeviceToDevice, s));
+  HIP_TRY(launch_copy_actions(tok, mg, p.B * p.D, tokens_out, margins_out, s));
   c->prefill_done = false;
   c->decode_done = true;
   return GVC_OK;
@@ -1279,33 +1281,25 @@ int32_t gvc_margin_gate(gvc_ctx* c, float theta, int32_t reduce, float* margin_o
   if (reduce != GVC_REDUCE_MEAN && reduce != GVC_REDUCE_MIN) return fail(GVC_EINVAL, "bad reduce");
   if (!c->decode_done) return fail(GVC_ESTATE, "margin_gate needs a decode first");
   const Plan& p = c->p;
-  float* m = c->K<float>(p.gate_m_off);
-  int* f = c->K<int>(p.gate_f_off);
   // The abort word of the single-launch decode pass stays set from a timed-out
   // barrier until this gate reports it: the gate kernel then invalidates every
   // episode instead of deciding on that decode's margins.
   const bool check_abort = c->persist_ran;
   uint32_t* abort_dev = c->K<uint32_t>(p.bar_off) + kDecodeAbortWord;
   HIP_TRY(launch_gate(c->S<float>(p.margins_off), p.B, p.D, theta, reduce == GVC_REDUCE_MIN, force,
-                      check_abort ? abort_dev : nullptr, c->S<int>(p.valid_off), m, f, c->stream));
-  std::vector<float> hm(p.B);
-  std::vector<int> hf(p.B);
-  HIP_TRY(hipMemcpyAsync(hm.data(), m, (size_t)p.B * 4, hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(hipMemcpyAsync(hf.data(), f, (size_t)p.B * 4, hipMemcpyDeviceToHost, c->stream));
-  if (check_abort)
-    HIP_TRY(hipMemcpyAsync(&c->abort_word, abort_dev, 4, hipMemcpyDeviceToHost, c->stream));
+                      check_abort ? abort_dev : nullptr, c->S<int>(p.valid_off), c->box_dev, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   if (check_abort) {
     c->persist_ran = false;
-    if (c->abort_word) {
+    if (c->box->abort_word) {
       c->decode_done = false;
       HIP_TRY(launch_fill_u32(abort_dev, 0u, 1, c->stream));   // reported: later passes may run again
       return fail(GVC_EDEVICE, "decode pass: grid barrier timed out; every episode's cache was invalidated");
     }
   }
   for (int b = 0; b < p.B; ++b) {
-    if (margin_out) margin_out[b] = hm[b];
-    if (fire_out) fire_out[b] = (uint8_t)(hf[b] != 0);
+    if (margin_out) margin_out[b] = c->box->margins[b];
+    if (fire_out) fire_out[b] = (uint8_t)(c->box->fired[b] != 0);
   }
   return GVC_OK;
 }

@@ -132,6 +132,19 @@ __device__ __forceinline__ void lse_merge(float& mx, float& sum, float mo, float
 
 }  // namespace gvc
 
+namespace gvc {
+// What the host waits for, in pinned host memory that the kernels write
+// directly (a context holds one).  As device buffers that were copied back,
+// each word cost a copy launch on the stream and, into pageable memory, a
+// wait of its own: a 4-layer 7B prompt pass and gate @@FIG@@.
+struct HostBox {
+  int counts[128];       // rows recomputed per layer (k_build_rows)
+  float margins[16];     // k_gate: per episode
+  int fired[16];
+  unsigned abort_word;   // k_gate: the decode launch's abort word
+};
+}  // namespace gvc
+
 #include "gvc_gemm.h"
 #include "gvc_decode.h"
 #include "gvc_launch.h"

@@ -24,7 +24,8 @@ hipError_t launch_rank_mask(const int* stats, int B, int N, int L, long long tau
                             int topk, float* score, const float* ent, int H, int n_instr, int* q_out, hipStream_t s);
 
 hipError_t launch_build_rows(const uint8_t* mask, const int* valid, int B, int L, int N, int P,
-                             int* rows, int* counts, int* ep_counts, int* ep_offsets, hipStream_t s);
+                             int* rows, int* counts, int* row_state, HostBox* box, int* ep_counts,
+                             int* ep_offsets, hipStream_t s);
 hipError_t launch_im2row(const uint8_t* frame, int views, int img, int patch, const int* idx, const int* pos,
                          int M, int P, int KB, bf16* x, hipStream_t s);
 hipError_t launch_layernorm(const float* src, int M, int d, const float* gain, const float* bias, float eps,
@@ -72,13 +73,16 @@ int decode_pass_threads();
 int decode_pass_score_offset();
 const void* decode_pass_kernel(int head_dim, int d_model);
 hipError_t launch_decode_pass(const DecodeArgs& a, int n_wg, hipStream_t s);   // cooperative launch
-// abort_word (or NULL): when set, every episode is invalidated and reported as fired with a NaN margin
 // Scratch of the allocation-free selection: per-patch statistics of at most
 // kSelectScratchEpisodes x kSelectScratchPatches patches (192 KiB per GPU).
 constexpr int kSelectScratchEpisodes = 16;
 constexpr int kSelectScratchPatches = 1024;
 hipError_t select_scratch(int** out);   // this device's copy (looked up once per device)
+// Margins, decisions and the abort word go to box.  abort_word (or NULL): when
+// set, every episode is invalidated and reported as fired with a NaN margin
 hipError_t launch_gate(const float* margins, int B, int D, float theta, int use_min, const int8_t* force,
-                       const unsigned* abort_word, int* valid, float* m_out, int* fire_out, hipStream_t s);
+                       const unsigned* abort_word, int* valid, HostBox* box, hipStream_t s);
+hipError_t launch_copy_actions(const int* tok, const float* mg, int n, int* tokens_out, float* margins_out,
+                               hipStream_t s);
 
 }  // namespace gvc

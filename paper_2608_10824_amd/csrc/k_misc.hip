@@ -70,10 +70,12 @@ __global__ void k_zero_kv_tail(bf16* __restrict__ k, bf16* __restrict__ v, size_
 // recomputed at layer l unless episode b has a valid cache, a mask is given,
 // pos is a visual token (1..N) and mask[b][l][pos-1] is set.  Writes the
 // compacted rows in (b, pos) order as three int arrays (idx, ep, pos) of
-// stride B*P, the per-layer count, and per-episode counts and offsets.
+// stride B*P, the per-layer count (also for the caller's state and the host),
+// and per-episode counts and offsets.
 __global__ __launch_bounds__(1024) void k_build_rows(const uint8_t* __restrict__ mask, const int* __restrict__ valid,
                                                      int B, int L, int N, int P, int* __restrict__ rows,
-                                                     int* __restrict__ counts, int* __restrict__ ep_counts,
+                                                     int* __restrict__ counts, int* __restrict__ row_state,
+                                                     HostBox* __restrict__ box, int* __restrict__ ep_counts,
                                                      int* __restrict__ ep_offsets) {
   __shared__ int warp_sums[16];
   __shared__ int s_base;
@@ -115,7 +117,11 @@ __global__ __launch_bounds__(1024) void k_build_rows(const uint8_t* __restrict__
     if (threadIdx.x == 1023) s_base = excl + flag;
     __syncthreads();
   }
-  if (threadIdx.x == 0) counts[l] = s_base;
+  if (threadIdx.x == 0) {
+    counts[l] = s_base;
+    row_state[l] = s_base;
+    box->counts[l] = s_base;
+  }
   __syncthreads();
   if (threadIdx.x < B) {
     const int b = threadIdx.x;
@@ -450,14 +456,15 @@ struct Force { signed char f[64]; };
 // the D positions; fire = !(m >= theta) unless forced; a fired episode's
 // cache becomes invalid.
 __global__ void k_gate(const float* __restrict__ margins, int B, int D, float theta, int use_min, Force force,
-                       const unsigned* __restrict__ abort_word, int* __restrict__ valid, float* __restrict__ m_out,
-                       int* __restrict__ fire_out) {
+                       const unsigned* __restrict__ abort_word, int* __restrict__ valid, HostBox* __restrict__ box) {
   const int b = threadIdx.x;
   if (b >= B) return;
-  if (abort_word && *abort_word) {   // the decode that produced the margins did not finish
-    valid[b] = 0;                    // invalidation is always safe: the next pass is full
-    m_out[b] = __builtin_nanf("");
-    fire_out[b] = 1;
+  const unsigned aborted = abort_word ? *abort_word : 0u;
+  if (b == 0) box->abort_word = aborted;
+  if (aborted) {    // the decode that produced the margins did not finish
+    valid[b] = 0;   // invalidation is always safe: the next pass is full
+    box->margins[b] = __builtin_nanf("");
+    box->fired[b] = 1;
     return;
   }
   const float* mr = margins + (size_t)b * D;
@@ -474,8 +481,17 @@ __global__ void k_gate(const float* __restrict__ margins, int B, int D, float th
   int fire = !(m >= theta);
   if (force.f[b] >= 0) fire = force.f[b] > 0;
   if (fire) valid[b] = 0;
-  m_out[b] = m;
-  fire_out[b] = fire;
+  box->margins[b] = m;
+  box->fired[b] = fire;
+}
+
+// The tokens and margins of a decode into the caller's buffers.
+__global__ void k_copy_actions(const int* __restrict__ tok, const float* __restrict__ mg, int n,
+                               int* __restrict__ tokens_out, float* __restrict__ margins_out) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    tokens_out[i] = tok[i];
+    margins_out[i] = mg[i];
+  }
 }
 
 // ------------------------------------------------------------------ launchers
@@ -513,9 +529,10 @@ hipError_t launch_zero_kv_tail(bf16* k, bf16* v, size_t n_blk, int kv_pad, int d
 }
 
 hipError_t launch_build_rows(const uint8_t* mask, const int* valid, int B, int L, int N, int P, int* rows,
-                             int* counts, int* ep_counts, int* ep_offsets, hipStream_t s) {
-  hipLaunchKernelGGL(k_build_rows, dim3(L), dim3(1024), 0, s, mask, valid, B, L, N, P, rows, counts, ep_counts,
-                     ep_offsets);
+                             int* counts, int* row_state, HostBox* box, int* ep_counts, int* ep_offsets,
+                             hipStream_t s) {
+  hipLaunchKernelGGL(k_build_rows, dim3(L), dim3(1024), 0, s, mask, valid, B, L, N, P, rows, counts, row_state, box,
+                     ep_counts, ep_offsets);
   return hipGetLastError();
 }
 
@@ -568,11 +585,16 @@ hipError_t launch_logits_reduce(const float* logits, int rows, int V, int bin_lo
 }
 
 hipError_t launch_gate(const float* margins, int B, int D, float theta, int use_min, const int8_t* force,
-                       const unsigned* abort_word, int* valid, float* m_out, int* fire_out, hipStream_t s) {
+                       const unsigned* abort_word, int* valid, HostBox* box, hipStream_t s) {
   Force f;
   for (int b = 0; b < 64; ++b) f.f[b] = (force && b < B) ? force[b] : -1;
-  hipLaunchKernelGGL(k_gate, dim3(1), dim3(64), 0, s, margins, B, D, theta, use_min, f, abort_word, valid, m_out,
-                     fire_out);
+  hipLaunchKernelGGL(k_gate, dim3(1), dim3(64), 0, s, margins, B, D, theta, use_min, f, abort_word, valid, box);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy_actions(const int* tok, const float* mg, int n, int* tokens_out, float* margins_out,
+                               hipStream_t s) {
+  hipLaunchKernelGGL(k_copy_actions, dim3(1), dim3(256), 0, s, tok, mg, n, tokens_out, margins_out);
   return hipGetLastError();
 }
 
