@@ -84,7 +84,7 @@ struct Plan {
   size_t rows_off, counts_off, epc_off, epo_off, stats_off, score_off, x_off, q_off, o_off, r_off, act_off, xdec_off, xf_off,
       ssq_a_off, ssq_f_off, qraw_off, kraw_off, part_off, part_bytes,
       logits_off, rope_off, decrows_off, headrows_off, tokens_off, qkv3_off, bar_off,
-      hpart_off, ws_bytes;
+      hpart_off, red_off, ws_bytes;
 };
 
 Packed plan_packed(Bump& a, int N, int K) {
@@ -249,6 +249,7 @@ int32_t make_plan(const gvc_desc* dsc, Plan& p) {
   p.qkv3_off = k.take((size_t)3 * p.B * d.d_model * 4);
   p.bar_off = k.take((size_t)kDecodeBarWords * 4);
   p.hpart_off = k.take((size_t)kDecodeMaxGrid * 8 * 4);
+  p.red_off = k.take((size_t)p.B * p.head_rows * kReduceRowWords * 4);
   {   // split-k partial sums (slices x rows x features) of the largest user:
       // gate/up, QKV or the down projection
     auto nsl = [](int KB, int want) { const int kps = (KB + want - 1) / want; return (size_t)((KB + kps - 1) / kps); };
@@ -913,7 +914,7 @@ int32_t gvc_init_cache(const gvc_desc* desc, const gvc_weights* wt, void* weight
   // GVC_POISON=1 (testing): every state and workspace byte starts as 0xFF
   // (NaN in fp32 and bf16, -1 in int32) instead of 0, except what the library
   // relies on starting at zero: the cache-valid flags, the decode barrier
-  // words, the key/value positions past the prompt (the prompt attention's
+  // words, the logits reduction's tickets, the key/value positions past the prompt (the prompt attention's
   // last key tile reads them with zero weight) and, when the FFN width is not
   // a multiple of 32, the activation fragments' padding columns.  A step that
   // reads anything else before writing it then yields NaN.
@@ -925,6 +926,7 @@ int32_t gvc_init_cache(const gvc_desc* desc, const gvc_weights* wt, void* weight
   if (c->poison) {
     INIT_TRY(launch_fill_u32(c->S<uint32_t>(p.valid_off), 0u, p.B, s));
     INIT_TRY(launch_fill_u32(c->K<uint32_t>(p.bar_off), 0u, kDecodeBarWords, s));
+    INIT_TRY(launch_fill_u32(c->K<uint32_t>(p.red_off), 0u, (size_t)p.B * p.head_rows * kReduceRowWords, s));
     INIT_TRY(launch_zero_kv_tail(c->S<bf16>(p.K_off), c->S<bf16>(p.V_off), (size_t)p.L * p.B * p.H, p.kv_pad, p.dh,
                                  p.P, s));
     if (p.d.ffn % 32)
@@ -1201,13 +1203,14 @@ int32_t gvc_decode_actions(gvc_ctx* c, int32_t* tokens_out, float* margins_out, 
   int* tok = c->K<int>(p.tokens_off);
   float* mg = c->S<float>(p.margins_off);
   const float* hl = c->S<float>(p.head_logits_off);
+  unsigned* red = c->K<unsigned>(p.red_off);
   const int full = p.d.norm_full_vocab ? 1 : 0;
   if (p.d.parallel_decode) {
-    HIP_TRY(launch_logits_reduce(hl, p.B * p.head_rows, p.V, p.bin_lo, full, tok, mg, p.D, 0, p.head_rows, s));
+    HIP_TRY(launch_logits_reduce(hl, p.B * p.head_rows, p.V, p.bin_lo, full, red, tok, mg, p.D, 0, p.head_rows, s));
     if (logits_out)
       HIP_TRY(hipMemcpyAsync(logits_out, hl, (size_t)p.B * p.D * p.V * 4, hipMemcpyDeviceToDevice, s));
   } else {
-    HIP_TRY(launch_logits_reduce(hl, p.B, p.V, p.bin_lo, full, tok, mg, p.D, 0, 1, s));
+    HIP_TRY(launch_logits_reduce(hl, p.B, p.V, p.bin_lo, full, red, tok, mg, p.D, 0, 1, s));
     if (logits_out)
       HIP_TRY(hipMemcpy2DAsync(logits_out, (size_t)p.D * p.V * 4, hl, (size_t)p.V * 4, (size_t)p.V * 4, p.B,
                                hipMemcpyDeviceToDevice, s));
@@ -1262,7 +1265,7 @@ int32_t gvc_decode_actions(gvc_ctx* c, int32_t* tokens_out, float* margins_out, 
       }
       int32_t r = run_gemm(c, hd, EPI_STORE, p.B, GVC_K_DECODE_HEAD);
       if (r) return r;
-      HIP_TRY(launch_logits_reduce(lg, p.B, p.V, p.bin_lo, full, tok, mg, p.D, j, 1, s));
+      HIP_TRY(launch_logits_reduce(lg, p.B, p.V, p.bin_lo, full, red, tok, mg, p.D, j, 1, s));
       if (logits_out)
         HIP_TRY(hipMemcpy2DAsync(logits_out + (size_t)j * p.V, (size_t)p.D * p.V * 4, lg, (size_t)p.V * 4,
                                  (size_t)p.V * 4, p.B, hipMemcpyDeviceToDevice, s));

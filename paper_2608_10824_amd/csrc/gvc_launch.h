@@ -65,9 +65,13 @@ hipError_t launch_attn_decode(const float* qraw, const float* kraw, bf16* kc, co
                               int B, int H, int head_dim, int kv_pad, int pos, bf16* o, int KB, hipStream_t s);
 hipError_t launch_embed_tokens(const bf16* embed, const int* tokens, int tok_stride, int B, int d, int V,
                                float* x, const float* gain, bf16* xn, int KB, float* ssq, hipStream_t s);
-hipError_t launch_logits_reduce(const float* logits, int rows, int V, int bin_lo, int full_vocab,
-                                int* tok_out, float* margin_out, int out_stride, int out_col,
-                                int rows_per_ep, hipStream_t s);
+// scratch: kReduceRowWords words per row, the first (a ticket) zero before the
+// first launch and left zero by every launch.
+constexpr int kReduceMaxParts = 64;
+constexpr int kReduceRowWords = 8 + 8 * kReduceMaxParts;
+hipError_t launch_logits_reduce(const float* logits, int rows, int V, int bin_lo, int full_vocab, unsigned* scratch,
+                                int* tok_out, float* margin_out, int out_stride, int out_col, int rows_per_ep,
+                                hipStream_t s);
 size_t decode_pass_lds_bytes(int act_bytes);
 int decode_pass_threads();
 int decode_pass_score_offset();

@@ -1,6 +1,7 @@
 // Row bookkeeping, normalisation, embedding, logits reduction, the gate and
 // the one-time weight packing.
 #include "gvc_kernels.h"
+#include "gvc_sync.h"
 
 namespace gvc {
 
@@ -376,51 +377,17 @@ __global__ void k_gather_visual(const bf16* __restrict__ src, const int* __restr
 }
 
 // ------------------------------------------------------------------ logits
-// One workgroup per head row: greedy bin token (ties to the lower id) and
-// margin p1 - p2 with the softmax normaliser over the whole vocabulary (Eq. 1).
+// Greedy bin token (ties to the lower id) and margin p1 - p2 of each head
+// row, with the softmax normaliser over the whole vocabulary (Eq. 1).  A row
+// is cut into parts of kReducePart logits, one workgroup each (one chunk of 4
+// per thread, so one load round trip; a workgroup per row of 32000 took 14
+// us); a part leaves its maximum, sum of exponentials and bin top-2 as a
+// record, and the row's last workgroup to arrive merges the records in part
+// order, so the result does not depend on the order of arrival.
 constexpr int kReduceThreads = 1024;
-constexpr int kReducePer = 8;   // chunks of 4 logits per thread loaded together
 
-// One pass over the row: every thread keeps its own running maximum, sum of
-// exponentials and bin top-2 over a strided set of float4 columns; the
-// partial results are merged across the wave, then across the 16 waves.
-__global__ __launch_bounds__(kReduceThreads) void k_logits_reduce(const float* __restrict__ logits, int V,
-                                                                  int bin_lo, int full_vocab, int* __restrict__ tok_out,
-                                                                  float* __restrict__ margin_out, int out_stride,
-                                                                  int out_col, int rows_per_ep) {
-  constexpr int NW = kReduceThreads / 64;
-  __shared__ float s_m[NW], s_s[NW], s_v1[NW], s_v2[NW];
-  __shared__ int s_i1[NW], s_i2[NW];
-  const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const float4* z4 = (const float4*)(logits + (size_t)r * V);
-  const int lo = full_vocab ? 0 : bin_lo;
-  const float NEG = -INFINITY;
-  float mx = NEG, sum = 0.f;
-  // running top-2 of the bins under `better` (a total order: value, then
-  // lower id), kept as scalars so that nothing goes to private memory
-  float v1 = NEG, v2 = NEG;
-  int i1 = 0x7fffffff, i2 = 0x7fffffff;
-  // each thread takes chunks tid, tid + T, ... in order; the loads of a batch
-  // of kReducePer chunks are all issued before any is used (one round trip)
-  const int n4 = V / 4;
-  for (int c0 = 0; c0 < n4; c0 += kReduceThreads * kReducePer) {
-    float4 q[kReducePer];
-#pragma unroll
-    for (int u = 0; u < kReducePer; ++u) q[u] = z4[min(c0 + u * kReduceThreads + tid, n4 - 1)];
-#pragma unroll
-    for (int u = 0; u < kReducePer; ++u) {
-      const int c = c0 + u * kReduceThreads + tid;
-      if (c < n4) {
-        const int i = c * 4;
-        const float e[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (i + j >= lo) lse_add(mx, sum, e[j]);
-          if (i + j >= bin_lo) top2_add(v1, i1, v2, i2, e[j], i + j);
-        }
-      }
-    }
-  }
+// Merges a record across the lanes of a wave; every lane ends with the same top-2.
+__device__ __forceinline__ void wave_merge(float& mx, float& sum, float& v1, int& i1, float& v2, int& i2) {
 #pragma unroll
   for (int m = 1; m < 64; m <<= 1) {
     lse_merge(mx, sum, __shfl_xor(mx, m), __shfl_xor(sum, m));
@@ -429,23 +396,74 @@ __global__ __launch_bounds__(kReduceThreads) void k_logits_reduce(const float* _
     top2_add(v1, i1, v2, i2, w1, j1);
     top2_add(v1, i1, v2, i2, w2, j2);
   }
+}
+
+__global__ __launch_bounds__(kReduceThreads) void k_logits_reduce(const float* __restrict__ logits, int V,
+                                                                  int bin_lo, int full_vocab, unsigned* scratch,
+                                                                  int* __restrict__ tok_out,
+                                                                  float* __restrict__ margin_out, int out_stride,
+                                                                  int out_col, int rows_per_ep) {
+  constexpr int NW = kReduceThreads / 64;
+  __shared__ float s_m[NW], s_s[NW], s_v1[NW], s_v2[NW];
+  __shared__ int s_i1[NW], s_i2[NW];
+  const int r = blockIdx.y, part = blockIdx.x, parts = gridDim.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const float4* z4 = (const float4*)(logits + (size_t)r * V);
+  const int lo = full_vocab ? 0 : bin_lo;
+  float mx = -INFINITY, sum = 0.f, v1 = -INFINITY, v2 = -INFINITY;
+  int i1 = 0x7fffffff, i2 = 0x7fffffff;
+  const int n4 = V / 4;
+  // (a vocabulary of more than kReduceMaxParts parts: several chunks per thread)
+  for (int c = part * kReduceThreads + tid; c < n4; c += parts * kReduceThreads) {
+    const float4 q = z4[c];
+    const int i = c * 4;
+    const float e[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (i + j >= lo) lse_add(mx, sum, e[j]);
+      if (i + j >= bin_lo) top2_add(v1, i1, v2, i2, e[j], i + j);
+    }
+  }
+  wave_merge(mx, sum, v1, i1, v2, i2);
   if (lane == 0) {
     s_m[wv] = mx; s_s[wv] = sum;
     s_v1[wv] = v1; s_i1[wv] = i1; s_v2[wv] = v2; s_i2[wv] = i2;
   }
   __syncthreads();
-  if (tid == 0) {
-    float M = s_m[0], S = s_s[0];
-    v1 = s_v1[0]; i1 = s_i1[0]; v2 = s_v2[0]; i2 = s_i2[0];
-    for (int w = 1; w < NW; ++w) {
-      lse_merge(M, S, s_m[w], s_s[w]);
-      top2_add(v1, i1, v2, i2, s_v1[w], s_i1[w]);
-      top2_add(v1, i1, v2, i2, s_v2[w], s_i2[w]);
+  if (wv != 0) return;
+  const int w = min(lane, NW - 1);   // lanes past the waves hold nothing
+  const bool on = lane < NW;
+  mx = on ? s_m[w] : -INFINITY; sum = on ? s_s[w] : 0.f;
+  v1 = on ? s_v1[w] : -INFINITY; i1 = on ? s_i1[w] : 0x7fffffff;
+  v2 = on ? s_v2[w] : -INFINITY; i2 = on ? s_i2[w] : 0x7fffffff;
+  wave_merge(mx, sum, v1, i1, v2, i2);
+  if (parts > 1) {
+    unsigned* row = scratch + (size_t)r * kReduceRowWords;   // ticket, then the records
+    unsigned ticket = 0;
+    if (lane == 0) {
+      const unsigned rec[6] = {__float_as_uint(mx), __float_as_uint(sum), __float_as_uint(v1), (unsigned)i1,
+                               __float_as_uint(v2), (unsigned)i2};
+#pragma unroll
+      for (int i = 0; i < 6; ++i)
+        __hip_atomic_store(row + 8 + part * 8 + i, rec[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      wait_vmcnt<0>();   // the record is there before the ticket is taken
+      ticket = __hip_atomic_fetch_add(row, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    const float m = (__expf(v1 - M) - __expf(v2 - M)) / S;
+    if (__shfl((int)ticket, 0) != parts - 1) return;
+    const bool has = lane < parts;
+    unsigned rec[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+      rec[i] = __hip_atomic_load(row + 8 + min(lane, parts - 1) * 8 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    mx = has ? __uint_as_float(rec[0]) : -INFINITY; sum = has ? __uint_as_float(rec[1]) : 0.f;
+    v1 = has ? __uint_as_float(rec[2]) : -INFINITY; i1 = has ? (int)rec[3] : 0x7fffffff;
+    v2 = has ? __uint_as_float(rec[4]) : -INFINITY; i2 = has ? (int)rec[5] : 0x7fffffff;
+    wave_merge(mx, sum, v1, i1, v2, i2);
+    if (lane == 0) __hip_atomic_store(row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+  }
+  if (lane == 0) {
     const int o = (r / rows_per_ep) * out_stride + out_col + r % rows_per_ep;
     tok_out[o] = i1;
-    margin_out[o] = m;
+    margin_out[o] = (__expf(v1 - mx) - __expf(v2 - mx)) / sum;
   }
 }
 
@@ -577,10 +595,12 @@ hipError_t launch_embed_tokens(const bf16* embed, const int* tokens, int tok_str
   return hipGetLastError();
 }
 
-hipError_t launch_logits_reduce(const float* logits, int rows, int V, int bin_lo, int full_vocab, int* tok_out,
-                                float* margin_out, int out_stride, int out_col, int rows_per_ep, hipStream_t s) {
-  hipLaunchKernelGGL(k_logits_reduce, dim3(rows), dim3(kReduceThreads), 0, s, logits, V, bin_lo, full_vocab, tok_out,
-                     margin_out, out_stride, out_col, rows_per_ep);
+hipError_t launch_logits_reduce(const float* logits, int rows, int V, int bin_lo, int full_vocab, unsigned* scratch,
+                                int* tok_out, float* margin_out, int out_stride, int out_col, int rows_per_ep,
+                                hipStream_t s) {
+  const int parts = std::min((V + 4 * kReduceThreads - 1) / (4 * kReduceThreads), kReduceMaxParts);
+  hipLaunchKernelGGL(k_logits_reduce, dim3(parts, rows), dim3(kReduceThreads), 0, s, logits, V, bin_lo, full_vocab,
+                     scratch, tok_out, margin_out, out_stride, out_col, rows_per_ep);
   return hipGetLastError();
 }
 
