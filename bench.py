@@ -556,8 +556,8 @@ def main():
 
     d, F, V, L, P = cfg.d_model, cfg.ffn, cfg.vocab, cfg.n_layers, cfg.prompt_len
     traffic = stored_traffic(KERNEL_SOURCES)
-    # dominant kernel: the single-launch decode pass (all layers of one token),
-    # one launch per decode pass; algorithmic bytes = every layer's weights
+    # dominant kernel: the single-launch decode (all layers of each token), which
+    # the profile counts per pass; algorithmic bytes = every layer's weights
     # once + the K and V rows of positions 0..pos read by the attention,
     # averaged over the passes (pass j attends over P + j keys)
     n_pass = cfg.n_decode - 1
@@ -565,7 +565,7 @@ def main():
     # the pass also runs the final norm, the LM head and the token choice
     # (unless GVC_DECODE_FLAGS masks the head bit): V x d head weights read,
     # V logits written
-    head_fused = (int(os.environ.get("GVC_DECODE_FLAGS", "7")) & 4) != 0
+    head_fused = (int(os.environ.get("GVC_DECODE_FLAGS", "4")) & 4) != 0
     if head_fused:
         dk_bytes += V * d * 2 + V * 4
     dk_avg_s = dk_ms / 1e3 / max(dk_n, 1)

@@ -29,7 +29,8 @@
  *    gvc_step_prefill (it waits for the per-layer row counts, a few bytes,
  *    before enqueuing the layers) and gvc_read_state.
  *  - No call allocates device memory; gvc_init_cache allocates only the
- *    host context.
+ *    host context and a few hundred bytes of pinned host memory, which
+ *    gvc_destroy frees.
  *  - A context is not thread-safe; calls on one context must not overlap.
  *
  * Key slots per layer: kv_len = P + D - 1 (autoregressive) or P (parallel),

@@ -289,7 +289,7 @@ struct gvc_ctx {
   bool prefill_done = false;
   bool decode_done = false;
   int force_splits = 0;   // GVC_FORCE_SPLITS: waves splitting each GEMM's k range (4 or 8; testing)
-  int tile_shape = 0;     // GVC_BIG_TW: the tile kernel's shape of every launch, 1 .. 8 (testing; 0: chosen per launch)
+  int tile_shape = 0;     // GVC_BIG_TW: the tile kernel's shape of every launch, 1 .. 10 (testing; 0: chosen per launch)
   bool poison = false;    // GVC_POISON: arenas start as 0xFF bytes instead of zeros (testing)
   int validate = 0;       // GVC_VALIDATE: 1 = every prompt pass checks its row lists on the host, 2 = also
                           // alters the host copy first, so the check must fail (tests that it runs)

@@ -5,7 +5,7 @@
 namespace gvc {
 
 // ------------------------------------------------------------------ persistent decode pass
-// One single-token pass over all layers for one episode (k_decode.hip).
+// Single-token passes over all layers for one episode (k_decode.hip).
 constexpr int kDecodeMaxSeg = 8;       // weight blocks per workgroup per step
 constexpr int kDecodeMaxSegs = 5 * kDecodeMaxSeg;   // of a wave in one layer (4 steps) and the LM head
 constexpr int kDecodeXccWord = 544;    // barrier words: set when a workgroup is not on XCD blockIdx % 8

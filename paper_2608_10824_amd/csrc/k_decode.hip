@@ -16,7 +16,7 @@
 // arithmetic, so its time is set by how continuously HBM is kept busy.  As
 // separate launches, each step of a layer pays a launch gap, a ramp-up and a
 // tail.  Here the weights never wait for the data: each compute wave streams
-// its share of every matrix of every layer, in order, into a ring of 16
+// its share of every matrix of every layer, in order, into a ring of 12
 // one-KiB fragments in LDS with direct global->LDS loads, and the ring keeps
 // running across the grid-wide barriers that separate the steps.  Only the
 // multiply waits for the activation vector.  The weight loads are marked
@@ -70,9 +70,9 @@ namespace {
 
 constexpr int kWaves = 8;                      // compute waves
 constexpr int kThreads = (kWaves + 1) * 64;    // plus the synchronising wave
-// Weight fragments in flight per compute wave.  Measured on the 7B pass
-// (µs per pass): 4: 2862, 6: 2844, 8: 2790, 10: 2799, 11: 2807, 12: 2786,
-// 13: 2804, 14: 2816, 16: 2857.
+// Weight fragments in flight per compute wave.  Four already keep HBM busy
+// while it streams (a copy-free probe: 6.9 TB/s); more are what the barriers'
+// windows can hide.  7B pass: 8: 2703 us, 10: 2714, 12: 2709, 14: 2724, 16: 2715.
 constexpr int kRing = 12;
 constexpr int kSC1 = 16;                       // buffer cache policy: device-coherent access
 constexpr int kSC0 = 1;                        // buffer cache policy: coherent within an XCD
