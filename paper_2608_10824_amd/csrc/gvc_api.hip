@@ -246,7 +246,7 @@ int32_t make_plan(const gvc_desc* dsc, Plan& p) {
   p.decrows_off = k.take((size_t)p.D * 3 * p.B * 4);
   p.headrows_off = k.take((size_t)3 * p.B * p.head_rows * 4);
   p.tokens_off = k.take((size_t)p.B * p.D * 4);
-  p.qkv3_off = k.take((size_t)3 * p.B * d.d_model * 4);
+  p.qkv3_off = k.take((size_t)3 * kDecodeQkvSlots * d.d_model * 4);
   p.bar_off = k.take((size_t)kDecodeBarWords * 4);
   p.hpart_off = k.take((size_t)kDecodeMaxGrid * 8 * 4);
   p.red_off = k.take((size_t)p.B * p.head_rows * kReduceRowWords * 4);

@@ -12,6 +12,7 @@ constexpr int kDecodeXccWord = 544;    // barrier words: set when a workgroup is
 constexpr int kDecodePoisonWord = 576; // barrier words: set when a head contribution was not finite
 constexpr int kDecodeHeadWord = 1024;  // barrier words: per-head counters, 32 words apart
 constexpr int kDecodeMaxHeads = 64;
+constexpr int kDecodeQkvSlots = 16;    // copies of the q, k, v exchange
 constexpr int kDecodeMaxGrid = 1024;   // workgroups of one pass (per-workgroup head records)
 // The abort flag is the last barrier word: the others are zeroed before a launch
 // sequence, it stays set until the gate that follows has reported it.
@@ -37,7 +38,7 @@ struct DecodeArgs {
   int n_pass;                  // passes of this launch, at positions pos, pos + 1, ... (1 without kDecodeHead)
   float* x;                    // [d] layer input / output (in place)
   unsigned long long* racc;    // [d] sum of the heads' attention-output contributions, int64 in 2^-32 units
-  float* qkv;                  // [3d] q, k, v before RoPE
+  float* qkv;                  // [kDecodeQkvSlots][3d] q, k, v before RoPE
   bf16* act;                   // [F] SwiGLU output
   unsigned* bar;               // kDecodeBarWords barrier words
   unsigned bar_base;           // grid barriers completed by earlier launches since the words were zeroed

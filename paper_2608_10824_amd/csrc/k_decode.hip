@@ -741,7 +741,6 @@ __global__ __launch_bounds__(kThreads) void k_decode_pass(const DecodeArgs a) {
       }
     }
   } else {
-    const rsrc_t r_qkv = rsrc(a.qkv, (size_t)3 * d * 4);
     unsigned nbar = 0, nhbar = 0;
     // grid barrier; the compute waves read the outcome after the block barrier
     auto barrier = [&]() -> bool {
@@ -781,6 +780,12 @@ __global__ __launch_bounds__(kThreads) void k_decode_pass(const DecodeArgs a) {
         block_sync();
         block_sync();   // partial sums ready
         if (attn) {
+          // Within an XCD q, k and v are read through this CU's L1: the layers
+          // take turns on kDecodeQkvSlots copies, so that the lines a layer reads
+          // were last read that many layers before and are gone from it (one
+          // copy and an L1 invalidation per layer cost the 7B step 280 us).
+          const rsrc_t r_qkv =
+              rsrc(a.qkv + (size_t)((pass * a.L + l) % kDecodeQkvSlots) * 3 * d, (size_t)3 * d * 4);
           for (int s0 = 0; s0 < nseg0; s0 += 4) {
             const int s = s0 + (lane >> 4), t = lane & 15;
             if (s < nseg0) {
