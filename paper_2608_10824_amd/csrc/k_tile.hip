@@ -284,8 +284,14 @@ constexpr TileShape kTiles[] = {
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 constexpr int kSlicedTiles = 5;   // the first ones also have an SL form (its totals fit the registers)
 
+// Workgroups of a launch, as if the fullest XCD's were on each of the 8: all
+// tiles of a weight tile run on one XCD (12-block tiles of the 7B output
+// projection are 22 weight tiles, three on six XCDs and two on the others:
+// 4416 rows take three rounds, 346 us on average with the down projection,
+// where 16-block tiles take two, 262).
 static int tile_count(const GemmArgs& a, const TileShape& t) {
-  return (2 * a.n_pairs + t.wblk - 1) / t.wblk * ((a.mblocks + t.tblk - 1) / t.tblk);
+  const int ntiles = (2 * a.n_pairs + t.wblk - 1) / t.wblk;
+  return (ntiles + 7) / 8 * 8 * ((a.mblocks + t.tblk - 1) / t.tblk);
 }
 
 // Time of a launch in ns: whole rounds of resident workgroups, then the rest,
