@@ -246,7 +246,9 @@ int32_t make_plan(const gvc_desc* dsc, Plan& p) {
   p.decrows_off = k.take((size_t)p.D * 3 * p.B * 4);
   p.headrows_off = k.take((size_t)3 * p.B * p.head_rows * 4);
   p.tokens_off = k.take((size_t)p.B * p.D * 4);
-  p.qkv3_off = k.take((size_t)3 * kDecodeQkvSlots * d.d_model * 4);
+  // exchange of the single-launch decode: a copy per layer step of a launch
+  const int dec_passes = p.B == 1 && !d.parallel_decode ? std::min(p.D - 1, decode_launch_passes(p.L)) : 0;
+  p.qkv3_off = k.take((size_t)dec_passes * p.L * 3 * d.d_model * 4);
   p.bar_off = k.take((size_t)kDecodeBarWords * 4);
   p.hpart_off = k.take((size_t)kDecodeMaxGrid * 8 * 4);
   p.red_off = k.take((size_t)p.B * p.head_rows * kReduceRowWords * 4);
@@ -1220,10 +1222,11 @@ int32_t gvc_decode_actions(gvc_ctx* c, int32_t* tokens_out, float* margins_out, 
       // every barrier word but the abort word, which stays set until a gate reports it
       HIP_TRY(launch_fill_u32(c->K<uint32_t>(p.bar_off), 0u, kDecodeAbortWord, s));
     }
-    // The single-launch decode runs all D - 1 passes at once when it also
-    // chooses the tokens; else one pass per launch.
+    // The single-launch decode runs the passes together, up to its limit, when
+    // it also chooses the tokens; else one pass per launch.
     const bool fused = c->persist && (c->dargs.flags & kDecodeHead) != 0;
-    for (int j = 1; j < p.D; j += fused ? p.D - 1 : 1) {
+    for (int j = 1, n = 1; j < p.D; j += n) {
+      if (fused) n = std::min(p.D - j, decode_launch_passes(p.L));
       const int* src = forced_tokens ? forced_tokens + (j - 1) : tok + (j - 1);
       const RowMap rows = c->dec_rows(j);
       const int pos = p.P + j - 1;
@@ -1236,7 +1239,7 @@ int32_t gvc_decode_actions(gvc_ctx* c, int32_t* tokens_out, float* margins_out, 
         DecodeArgs a = c->dargs;
         a.tok_in = src;
         a.forced = forced_tokens ? 1 : 0;
-        a.n_pass = fused ? p.D - 1 : 1;
+        a.n_pass = n;
         a.pos = pos;
         a.bar_base = (unsigned)((j - 1) * decode_grid_barriers(p.L, fused));
         a.hbar_base = (unsigned)((j - 1) * decode_head_barriers(p.L));
@@ -1248,7 +1251,7 @@ int32_t gvc_decode_actions(gvc_ctx* c, int32_t* tokens_out, float* margins_out, 
           HIP_TRY(launch_decode_pass(a, c->persist_wg, s));
         }
         c->persist_ran = true;
-        if (fused) break;
+        if (fused) continue;
         ProfScope ps(c, GVC_K_NORM);
         HIP_TRY(launch_rmsnorm(xdec, nullptr, p.B, p.d.d_model, c->W<float>(p.final_gain_off), p.d.rms_eps,
                                c->K<bf16>(p.x_off), p.KBd, c->big_gemm, s));

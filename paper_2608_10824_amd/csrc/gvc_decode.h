@@ -12,7 +12,12 @@ constexpr int kDecodeXccWord = 544;    // barrier words: set when a workgroup is
 constexpr int kDecodePoisonWord = 576; // barrier words: set when a head contribution was not finite
 constexpr int kDecodeHeadWord = 1024;  // barrier words: per-head counters, 32 words apart
 constexpr int kDecodeMaxHeads = 64;
-constexpr int kDecodeQkvSlots = 16;    // copies of the q, k, v exchange
+// Layer steps (passes x layers) of one launch.  Each has a copy of the q, k, v
+// exchange of its own, so that no line of it is read twice in a launch; at the
+// 7B shape a launch of 8 passes takes 12.6 MB of them, 0.01% of the weights it
+// streams.  More passes go to further launches.
+constexpr int kDecodeMaxSteps = 256;
+constexpr int decode_launch_passes(int L) { return kDecodeMaxSteps / L; }   // L <= 128
 constexpr int kDecodeMaxGrid = 1024;   // workgroups of one pass (per-workgroup head records)
 // The abort flag is the last barrier word: the others are zeroed before a launch
 // sequence, it stays set until the gate that follows has reported it.
@@ -35,10 +40,11 @@ struct DecodeArgs {
   const bf16* embed;           // [V][d] token embedding table: a pass starts from its token's row
   const int* tok_in;           // token of the first pass; with `forced`, of pass p at tok_in[p]
   int forced;                  // 1: every pass takes its token from tok_in, 0: from the pass before
-  int n_pass;                  // passes of this launch, at positions pos, pos + 1, ... (1 without kDecodeHead)
+  int n_pass;                  // passes of this launch, at positions pos, pos + 1, ... (1 without kDecodeHead),
+                               // n_pass * L <= kDecodeMaxSteps
   float* x;                    // [d] layer input / output (in place)
   unsigned long long* racc;    // [d] sum of the heads' attention-output contributions, int64 in 2^-32 units
-  float* qkv;                  // [kDecodeQkvSlots][3d] q, k, v before RoPE
+  float* qkv;                  // [n_pass][L][3d] q, k, v before RoPE
   bf16* act;                   // [F] SwiGLU output
   unsigned* bar;               // kDecodeBarWords barrier words
   unsigned bar_base;           // grid barriers completed by earlier launches since the words were zeroed

@@ -2,7 +2,8 @@
 // single-token passes of a control step (Sec. IV, autoregressive action
 // decode) in one cooperative launch of one workgroup per compute unit.
 //
-// With the LM head inside, the launch runs all the passes: a pass's token is
+// With the LM head inside, the launch runs all the passes (up to
+// kDecodeMaxSteps / L of them; longer decodes take several launches): a pass's token is
 // known to every workgroup after the head's grid barrier (each merges the
 // workgroups' records itself), so the next pass only needs the embedding row
 // written before its first barrier, and the weight ring runs on from one pass
@@ -121,7 +122,8 @@ __device__ __forceinline__ u32x4 ld_b128(rsrc_t r, int off) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kSC1);
 }
 // Exchange within one XCD (device-coherent when `xl` is false): stores are
-// written through to the XCD's L2, loads with sc0 miss in the CU's L1.
+// written through to the XCD's L2; loads may hit in the CU's L1, so a launch
+// reads a line only once, after it was written.
 __device__ __forceinline__ float ld_f32_x(rsrc_t r, int off, bool xl) {
   return xl ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kSC0))
             : __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kSC1));
@@ -780,12 +782,12 @@ __global__ __launch_bounds__(kThreads) void k_decode_pass(const DecodeArgs a) {
         block_sync();
         block_sync();   // partial sums ready
         if (attn) {
-          // Within an XCD q, k and v are read through this CU's L1: the layers
-          // take turns on kDecodeQkvSlots copies, so that the lines a layer reads
-          // were last read that many layers before and are gone from it (one
-          // copy and an L1 invalidation per layer cost the 7B step 280 us).
-          const rsrc_t r_qkv =
-              rsrc(a.qkv + (size_t)((pass * a.L + l) % kDecodeQkvSlots) * 3 * d, (size_t)3 * d * 4);
+          // Within an XCD q, k and v are read through this CU's L1, which a store
+          // of another CU does not reach.  So every layer of every pass has a copy
+          // of its own: its lines are first read here, after head_sync, and the L1
+          // starts a launch empty (one copy and an L1 invalidation per layer cost
+          // the 7B step 280 us).
+          const rsrc_t r_qkv = rsrc(a.qkv + (size_t)(pass * a.L + l) * 3 * d, (size_t)3 * d * 4);
           for (int s0 = 0; s0 < nseg0; s0 += 4) {
             const int s = s0 + (lane >> 4), t = lane & 15;
             if (s < nseg0) {

@@ -83,3 +83,51 @@ def test_keys_and_values_of_another_decode_leave_no_trace(heads, head_dim):
     assert float(err.max()) <= 2e-2, err
     for s in (s1, s2, s3):
         s.close()
+
+
+@pytest.mark.parametrize("layers,heads,head_dim,n_decode", [(1, 8, 64, 40), (1, 8, 64, 300), (1, 16, 128, 34),
+                                                            (2, 8, 128, 140), (3, 24, 64, 90)])
+def test_many_passes_of_a_launch_match_a_launch_per_pass(layers, heads, head_dim, n_decode):
+    """Heads whose workgroups share a compute die exchange q, k and v through
+    its caches.  A launch of many passes over few layers must read each pass's
+    own: the keys and values appended must equal bit for bit those of launches
+    of one pass each (GVC_DECODE_FLAGS=0, whose caches start empty), with short
+    prompts, where nothing else pushes a line out, and with more layer steps
+    than one launch takes (256); logits within the rounding of the two heads'
+    sums."""
+    from paper_2608_10824_amd import gvc
+    from paper_2608_10824_amd.session import Session
+    cfg = synth.config_c1().with_(n_layers=layers, n_heads=heads, d_model=heads * head_dim, img=28, n_text=4,
+                                  n_decode=n_decode)
+    w = synth.model_weights(cfg, device=DEV)
+    si = synth.step_inputs(cfg, 2)
+    fp, ids = si["frame_prev"].to(DEV), si["text_ids"].to(DEV)
+    g = torch.Generator().manual_seed(layers * heads)
+    fed = torch.randint(0, cfg.vocab, (1, n_decode), generator=g, dtype=torch.int32).to(DEV)
+
+    def decode(flags, forced):
+        with pytest.MonkeyPatch.context() as mp:
+            if flags is not None:
+                mp.setenv("GVC_DECODE_FLAGS", flags)
+            s = Session(cfg, w, device=DEV)
+        s.step_prefill(fp, ids)
+        t, _, lg = s.decode_actions(logits=True, forced_tokens=forced)
+        out = [t.clone(), lg.clone()] + [s.read(i, l).clone() for l in range(layers)
+                                         for i in (gvc.STATE_K, gvc.STATE_V)]
+        s.margin_gate()   # no barrier timed out
+        s.close()
+        return out
+
+    got, ref = decode(None, fed), decode("0", fed)
+    for x, y in zip(got[2:], ref[2:]):
+        assert torch.equal(x, y)
+    # The hidden states are the same, but the two final norms add the squares in
+    # different orders (a few ulp), so about one value in 10^4 rounds to the
+    # other bf16 neighbour: 2^-8 of a value.  Up to 4 such values of twice the
+    # root mean square in a row of d move its logits by 2 * 2 * 2^-8 / sqrt(d).
+    err = (got[1] - ref[1]).norm(dim=-1) / ref[1].norm(dim=-1)
+    assert float(err.max()) <= 2 ** -6 / cfg.d_model ** 0.5, float(err.max())
+    # freely chosen tokens of a decode that takes several launches feed back the same way
+    free = decode(None, None)
+    for x, y in zip(free, decode(None, free[0])):
+        assert torch.equal(x, y)
