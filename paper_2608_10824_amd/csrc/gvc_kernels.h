@@ -113,7 +113,8 @@ __device__ __forceinline__ void top2_add(float& v1, int& i1, float& v2, int& i2,
   i2 = ni2;
 }
 
-// Running (max, sum of exp(z - max)) pair; a term at -inf contributes 0.
+// Running (max, sum of exp(z - max)) pair; a term at -inf contributes 0, a NaN
+// makes the sum NaN.  While the maximum is -inf the sum is 0 or NaN.
 __device__ __forceinline__ void lse_add(float& mx, float& sum, float v) {
   if (v > mx) {
     sum = sum * __expf(mx - v) + 1.f;
@@ -125,8 +126,7 @@ __device__ __forceinline__ void lse_add(float& mx, float& sum, float v) {
 
 __device__ __forceinline__ void lse_merge(float& mx, float& sum, float mo, float so) {
   const float m = fmaxf(mx, mo);
-  if (m == -INFINITY) return;
-  sum = (mx == -INFINITY ? 0.f : sum * __expf(mx - m)) + (mo == -INFINITY ? 0.f : so * __expf(mo - m));
+  sum = (mx == -INFINITY ? sum : sum * __expf(mx - m)) + (mo == -INFINITY ? so : so * __expf(mo - m));
   mx = m;
 }
 
