@@ -338,7 +338,8 @@ int32_t gvc_profile_begin(gvc_ctx* ctx, int32_t cls, int32_t max_launches);
  * GVC_ESTATE if no profile is running, GVC_EDEVICE. */
 int32_t gvc_profile_end(gvc_ctx* ctx, double* total_ms, int32_t* launches);
 
-/* Frees the host context.  Device memory stays with the caller. */
+/* Frees the host context, after the work running on the GPU (its pinned memory
+ * is freed).  Device memory stays with the caller. */
 int32_t gvc_destroy(gvc_ctx* ctx);
 
 /* Thread-local text of the last error ("" if none). */

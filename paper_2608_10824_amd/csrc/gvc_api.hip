@@ -27,6 +27,15 @@ int32_t fail(int32_t code, const std::string& msg) {
     if (e_ != hipSuccess) return fail(GVC_EDEVICE, std::string(#x) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
+// While it lives, this thread's allocations are accepted, and left out of the
+// capture, when a stream of the process is being captured: a context may be
+// made or destroyed then (the pinned words below belong to no captured work).
+struct CaptureRelaxed {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  CaptureRelaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~CaptureRelaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 constexpr size_t kAlign = 256;
 constexpr int kMaxNT = 5;   // token blocks per GEMM workgroup (best of 2..16 on the 7B prompt pass)
 // Vision front-end launches of up to 256 rows (one view) with at most 64
@@ -319,6 +328,7 @@ struct gvc_ctx {
   HostBox* box = nullptr;         // pinned host memory (host address) and where the kernels see it
   HostBox* box_dev = nullptr;
   ~gvc_ctx() {
+    const CaptureRelaxed relaxed;
     if (box) (void)hipHostFree(box);
   }
   // launch timing of one kernel class (gvc_profile_begin / _end)
@@ -899,7 +909,10 @@ int32_t gvc_init_cache(const gvc_desc* desc, const gvc_weights* wt, void* weight
   } while (0)
 
   INIT_TRY(hipGetDevice(&c->device));
-  INIT_TRY(hipHostMalloc(reinterpret_cast<void**>(&c->box), sizeof(HostBox), hipHostMallocMapped));
+  {
+    const CaptureRelaxed relaxed;
+    INIT_TRY(hipHostMalloc(reinterpret_cast<void**>(&c->box), sizeof(HostBox), hipHostMallocMapped));
+  }
   INIT_TRY(hipHostGetDevicePointer(reinterpret_cast<void**>(&c->box_dev), c->box, 0));
   if (const char* fs = getenv("GVC_FORCE_SPLITS")) c->force_splits = atoi(fs);
   c->big_gemm = p.B * p.P >= kBigRows;

@@ -111,3 +111,53 @@ def test_validation_hook_reports_a_bad_list(monkeypatch):
     assert e.value.code == gvc.GVC_EDEVICE and "row lists fail the host check" in str(e.value)
     assert "layer 0" in str(e.value)
     s.close()
+
+
+@pytest.mark.parametrize("own_thread", [True, False])
+@pytest.mark.parametrize("mode", ["global", "thread_local", "relaxed"])
+def test_context_made_and_destroyed_while_another_stream_is_captured(mode, own_thread):
+    """A context may be made, stepped and destroyed while a stream of the
+    process is being captured into a graph: its calls give what they give
+    otherwise, and the capture stays valid (the graph is replayed)."""
+    import threading
+
+    from paper_2608_10824_amd.session import Session
+    cfg = synth.config_c1()
+    w = synth.model_weights(cfg, device=DEV)
+    si = synth.step_inputs(cfg, 20)
+    fp, ids = si["frame_prev"].to(DEV), si["text_ids"].to(DEV)
+    got, errors = [], []
+
+    def step():
+        try:
+            s = Session(cfg, w, device=DEV)
+            s.step_prefill(fp, ids)
+            t, m, _ = s.decode_actions()
+            got.append((t.clone(), m.clone(), s.margin_gate()))
+            s.close()
+        except Exception as e:   # reported below, after the capture has ended
+            errors.append(e)
+
+    step()   # everything that loads on first use, and the arenas' memory
+    x = torch.zeros(64, device=DEV)
+    g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        g.capture_begin(capture_error_mode=mode)
+        x.add_(1)
+    try:
+        if own_thread:
+            step()
+        else:
+            t = threading.Thread(target=step)
+            t.start()
+            t.join()
+    finally:
+        with torch.cuda.stream(side):
+            g.capture_end()
+    assert not errors, errors
+    for _ in range(3):
+        g.replay()
+    torch.cuda.synchronize()
+    assert bool((x == 3).all())
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]) and got[0][2] == got[1][2]
