@@ -47,8 +47,8 @@ constexpr int kVitNT = 2;
 constexpr int kBigRows = 1024;  // sessions with at least this many prompt rows sum every projection over k in one go
 // The other sessions sum a prompt-pass projection in k slices fixed per matrix
 // shape (gate/up 2, QKV 4, down 8, output the shares of tile_gemm), whichever
-// kernel runs it: split-k launches (k_gemm_dx) and the per-pair kernel for
-// few rows, the tile kernel (tile_gemm_wanted) for more.
+// kernel runs it: split-k launches (k_gemm_dx), the per-pair kernel or the
+// tile kernel (gemm_route).
 constexpr int kSkGuSlices = 2;
 constexpr int kSkQkvSlices = 4, kSkDownSlices = 8;
 
@@ -262,12 +262,13 @@ int32_t make_plan(const gvc_desc* dsc, Plan& p) {
   p.hpart_off = k.take((size_t)kDecodeMaxGrid * 8 * 4);
   p.red_off = k.take((size_t)p.B * p.head_rows * kReduceRowWords * 4);
   {   // split-k partial sums (slices x rows x features) of the largest user:
-      // gate/up, QKV or the down projection
+      // gate/up, QKV, output or down projection
     auto nsl = [](int KB, int want) { const int kps = (KB + want - 1) / want; return (size_t)((KB + kps - 1) / kps); };
     const size_t gu = nsl(p.KBd, kSkGuSlices) * 2 * (size_t)((d.ffn + 15) / 16 * 16);
     const size_t qkv = nsl(p.KBd, kSkQkvSlices) * 3 * (size_t)d.d_model;
     const size_t down = nsl(p.KBf, kSkDownSlices) * (size_t)d.d_model;
-    p.part_bytes = (size_t)p.Mp * std::max({gu, qkv, down}) * 4;
+    const size_t outp = nsl(p.KBd, 8) * (size_t)d.d_model;   // (8 waves' k shares, see gemm_route)
+    p.part_bytes = (size_t)p.Mp * std::max({gu, qkv, down, outp}) * 4;
     p.part_off = k.take(p.part_bytes);
   }
   if (p.vit) {
@@ -313,11 +314,12 @@ struct gvc_ctx {
   // (GVC_SK=0, GVC_SK_QKV=0, GVC_SK_DOWN=0: the per-pair kernel, at every
   // row count; testing)
   bool sk_gemm = true, sk_qkv = true, sk_down = true;
-  // those and the output projection on the tile kernel where tile_gemm_wanted
-  // says so, and the down projection in tall tiles (GVC_SK_TALL=0: split-k in
-  // tiles of 10 token blocks and the per-pair kernel only; testing)
-  bool sk_tall = true;
-  // GVC_SK_CORE=0: what split-k would run goes to the tile kernel (testing)
+  // launches above 160 rows on the kernel that gemm_route names, split-k ones of
+  // the output and down projections in tall tiles (GVC_SK_TALL=0: split-k in
+  // tiles of 10 token blocks and the per-pair kernel only; 2: those two in tall
+  // tiles wherever these fit; testing)
+  int sk_tall = 1;
+  // GVC_SK_CORE=0: all four projections on the tile kernel at every row count (testing)
   bool tile_always = false;
   // persistent decode pass (k_decode.hip): eligible shape, its grid and LDS
   bool persist = false;
@@ -417,35 +419,48 @@ GemmArgs base_args(const gvc_ctx* c) {
 }
 
 
-// A prompt-pass projection of a split-k session: split-k launches (shape
-// SK_WIDE or SK_NARROW), or the tile kernel adding up the same slices, which
-// depend only on the matrix shape.  shape 0: the per-pair kernel, whose k
-// shares are the slices, or the tile kernel.
+// A prompt-pass projection of a split-k session, in k slices that depend only
+// on the matrix shape, on the kernel that gemm_route names: split-k launches
+// (shape SK_WIDE or SK_NARROW) or the tile kernel; with shape 0 (the output
+// projection) also the per-pair kernel, whose k shares are then the slices.
 int32_t run_gemm(gvc_ctx* c, GemmArgs& a, int epi, int M, int cls, bool big = false);
 int32_t run_gemm_sliced(gvc_ctx* c, GemmArgs& a, int epi, int M, int cls, int slices, int shape) {
   if (M <= 0) return GVC_OK;
   const Plan& p = c->p;
-  if (shape == 0) tile_gemm(a, M, c->force_splits);
-  if (slices == 0) slices = a.splits;
+  const bool pairs = shape == 0;
+  int NT = 0;
+  if (pairs) {
+    tile_gemm(a, M, c->force_splits);
+    NT = nt_of(a);
+    slices = a.splits;
+    shape = SK_NARROW;
+  }
   a.M = M;
   a.mblocks = (M + 15) / 16;
-  const int kps = (a.KB + slices - 1) / slices;
-  if ((c->sk_tall && tile_gemm_wanted(a, epi)) || (c->tile_always && shape != 0)) {
-    a.sk_steps = kps;
+  a.sk_steps = (a.KB + slices - 1) / slices;
+  a.sk_slices = (a.KB + a.sk_steps - 1) / a.sk_steps;
+  const int nblk = a.wblk[0] * (a.map == MAP_QKV ? 3 : (a.map == MAP_GU ? 2 : 1));
+  const int gb = gemm_sk_group_blocks(shape);
+  a.sk_groups = (nblk + gb - 1) / gb;
+  a.sk_shape = shape;
+  a.sk_tall = 0;
+  int cus = 0;
+  HIP_TRY(device_cus(cus));
+  GemmRoute route = pairs ? GemmRoute::kPairs : GemmRoute::kSplit;
+  if (c->tile_always) route = GemmRoute::kTile;
+  else if (c->sk_tall) route = gemm_route(a, epi, pairs, NT, cus);
+  if (c->sk_tall == 2 && epi == EPI_RESID && gemm_sk_tall_rows(M) && (!pairs || a.splits == 8)) {
+    route = GemmRoute::kSplit;
+    a.sk_tall = 1;
+  }
+  if (route == GemmRoute::kPairs) return run_gemm(c, a, epi, M, cls);
+  if (route == GemmRoute::kTile) {
     a.tile_shape = c->tile_shape;
     ProfScope ps(c, cls);
     HIP_TRY(launch_gemm_tile(a, epi, c->stream));
     return GVC_OK;
   }
-  if (shape == 0) return run_gemm(c, a, epi, M, cls);
-  a.sk_steps = kps;
-  a.sk_slices = (a.KB + kps - 1) / kps;
-  const int nblk = a.wblk[0] * (a.map == MAP_QKV ? 3 : (a.map == MAP_GU ? 2 : 1));
-  const int gb = gemm_sk_group_blocks(shape);
-  a.sk_groups = (nblk + gb - 1) / gb;
   a.part = c->K<float>(p.part_off);
-  a.sk_shape = shape;
-  a.sk_tall = c->sk_tall ? 1 : 0;
   a.part_ld = nblk * 16;
   a.part_rows = a.mblocks * 16;
   if ((size_t)a.sk_slices * a.part_rows * a.part_ld * 4 > p.part_bytes) return fail(GVC_EINVAL, "split-k buffer");
@@ -920,7 +935,7 @@ int32_t gvc_init_cache(const gvc_desc* desc, const gvc_weights* wt, void* weight
   if (const char* sc = getenv("GVC_SK_CORE")) c->tile_always = atoi(sc) == 0;
   if (const char* e = getenv("GVC_SK_QKV")) c->sk_qkv = atoi(e) != 0;
   if (const char* e = getenv("GVC_SK_DOWN")) c->sk_down = atoi(e) != 0;
-  if (const char* e = getenv("GVC_SK_TALL")) c->sk_tall = atoi(e) != 0;
+  if (const char* e = getenv("GVC_SK_TALL")) c->sk_tall = atoi(e);
   if (const char* tw = getenv("GVC_BIG_TW")) c->tile_shape = atoi(tw);
   if (const char* g = getenv("GVC_GEMM")) {
     if (!strcmp(g, "big")) c->big_gemm = true;

@@ -75,15 +75,12 @@ struct GemmArgs {
   int sk_slices, sk_steps, sk_groups, part_ld, part_rows;
   int tile_shape;       // tile kernel: 1 + index of the shape, 0 = chosen per launch (testing)
   int sk_shape;         // k_gemm_dx work split: SK_WIDE (12 blocks) or SK_NARROW (8), see gemm_sk_group_blocks()
-  int sk_tall;          // SK_NARROW at 11-18 token blocks: one tile of 18 blocks per k slice instead
-                        // of two of 10 (0 = always tiles of 10)
+  int sk_tall;          // SK_NARROW at 11-18 token blocks: one tile of 18 blocks per k slice instead of two of 10
   EpiArgs e;
 };
 
-// A residual projection of more k steps than this stays on split-k up to 288
-// rows (tile_gemm_wanted): the 7B output projection has 128, the down
-// projection 344.
-constexpr int kTileLongK = 192;
+// The kernels that run a prompt-pass projection of a split-k session.
+enum class GemmRoute { kPairs, kSplit, kTile };
 
 // k-steps per pipelined register chunk for a tile of NT blocks of 16 token rows.
 constexpr int gemm_pf(int NT) { return NT == 1 ? 4 : (NT <= 3 ? 4 : (NT <= 6 ? 2 : 1)); }

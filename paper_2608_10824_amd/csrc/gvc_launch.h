@@ -40,17 +40,24 @@ hipError_t launch_rmsnorm(const float* src, const int* idx, int M, int d, const 
 // Tiled GEMM (k_tile.hip): EPI_QKV, EPI_RESID, EPI_SILU, EPI_EMBED; with
 // a.sk_steps > 0 summed in slices of that many k steps.
 hipError_t launch_gemm_tile(const GemmArgs& a, int epi, hipStream_t s);
-// Whether a projection of a split-k session (a.M, a.mblocks, a.n_pairs, a.KB)
-// takes the tile kernel, in slices, instead of split-k.
-bool tile_gemm_wanted(const GemmArgs& a, int epi);
+hipError_t device_cus(int& cus);   // compute units of the GPU (looked up once)
+// The kernel of a projection of a split-k session; a has M, mblocks, n_pairs,
+// KB, sk_steps, sk_slices and sk_groups (SK_NARROW for a residual projection),
+// and gets sk_tall.  pairs: the launch is the per-pair kernel's (splits, mtiles, tiles
+// of NT token blocks) unless another is chosen, else split-k's.
+GemmRoute gemm_route(GemmArgs& a, int epi, bool pairs, int NT, int cus);
 // Split-k prompt-pass GEMM (k_gemm_dx, then the slice sum and epilogue);
 // workgroups own groups of gemm_sk_group_blocks(a.sk_shape) weight blocks.
 hipError_t launch_gemm_sk(const GemmArgs& a, int epi, hipStream_t s);
 int gemm_sk_group_blocks(int sk_shape);
-// Whether a narrow split-k launch of M rows takes one tall tile per k slice
+// Whether a narrow split-k launch of M rows can take one tall tile per k slice
 // (161-288 rows).
 bool gemm_sk_tall_rows(int M);
 hipError_t launch_gemm(const GemmArgs& a, int epi, int NT, hipStream_t s);
+// Expected times in a prompt pass, in us: a narrow split-k launch with its slice
+// sum, and a launch of the per-pair kernel.
+float gemm_sk_narrow_time(const GemmArgs& a, bool tall, int cus);
+float gemm_ks_time(const GemmArgs& a, int NT, int cus);
 // Stage 2 signal of one layer: tv[b * tv_bstride + h * N + n] = sum over the
 // T1 instruction rows after the image of their softmax probability on visual
 // key n (1 <= T1 <= 32, N + T1 < 640).

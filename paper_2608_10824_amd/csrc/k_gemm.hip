@@ -372,14 +372,27 @@ bool gemm_sk_tall_rows(int M) {
   return mblocks > kSkT && mblocks <= kSkTallT;
 }
 
+// Fitted to prompt passes of widths 512-5120 at 161-900 rows that differ in the
+// kernel of one residual projection (see gemm_route): a ramp per round of
+// workgroups, the weights and MFMAs of all workgroups spread over the CUs (tall
+// tiles: of whole rounds), and the partial sums' way through memory.
+float gemm_sk_narrow_time(const GemmArgs& a, bool tall, int cus) {
+  const float mb = 4e-6f * a.M * a.wblk[0] * 16 * a.sk_slices;   // megabytes of partial sums
+  const int n = a.sk_groups * a.sk_slices * (tall ? 1 : (a.mblocks + kSkT - 1) / kSkT);
+  const int rounds = (n + cus - 1) / cus;
+  if (tall) return 14.5f + 0.58f * rounds * a.sk_steps + 0.31f * mb;
+  return 10.3f + 6.4f * rounds + 0.457f * n * a.sk_steps / cus + 0.16f * mb;
+}
+
 int gemm_sk_group_blocks(int sk_shape) { return sk_shape == SK_WIDE ? kDxWideW : kDxNarrowW; }
 
 hipError_t launch_gemm_sk(const GemmArgs& a, int epi, hipStream_t s) {
   if (a.map == MAP_SINGLE || a.map == MAP_QKV_SINGLE || a.e.ssq_in || !a.part) return hipErrorInvalidValue;
+  if (a.sk_tall && (a.sk_shape != SK_NARROW || !gemm_sk_tall_rows(a.M))) return hipErrorInvalidValue;
   hipError_t e;
   if (a.sk_shape == SK_WIDE)
     e = launch_dx_core<kSkT, kDxWideW, 1, kDxKC, kDxD, kDxNXW, kDxWideR>(a, s);
-  else if (a.sk_tall && gemm_sk_tall_rows(a.M))
+  else if (a.sk_tall)
     e = launch_dx_core<kSkTallT, kDxNarrowW, 1, kDxKC, kDxTallNarrowD, kDxNXW, kDxNarrowR>(a, s);
   else
     e = launch_dx_core<kSkT, kDxNarrowW, 1, kDxKC, kDxD, kDxNXW, kDxNarrowR>(a, s);
@@ -444,6 +457,13 @@ static hipError_t launch_epi(const GemmArgs& a, int NT, hipStream_t s) {
     case 5: return launch_nt<EPI, 5>(a, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+// Fitted as gemm_sk_narrow_time: one workgroup of 8 waves to a CU, two of 4.
+float gemm_ks_time(const GemmArgs& a, int NT, int cus) {
+  const int n = a.n_pairs * a.mtiles;
+  if (a.splits != 8) return 7.7f + 0.2f * a.KB * ((n + 2 * cus - 1) / (2 * cus));
+  return 7.5f + (1.3f + (NT > 4 ? 0.108f : 0.076f) * a.KB) * ((n + cus - 1) / cus);
 }
 
 hipError_t launch_gemm(const GemmArgs& a, int epi, int NT, hipStream_t s) {

@@ -1,7 +1,6 @@
 // Tiled GEMM of the prompt pass for launches that fill the chip with whole
-// tiles: every projection of the many-row sessions, and QKV, gate/up, output
-// and down projections of the others from the row counts given at
-// tile_gemm_wanted() on.
+// tiles: every projection of the many-row sessions, and those launches of the
+// others that gemm_route() gives it.
 //
 // A workgroup of WW x WT waves owns WW * WP weight pairs x WT * TB blocks of
 // 16 token rows and walks the whole k range in order.  Every k step, both
@@ -298,11 +297,15 @@ static int tile_count(const GemmArgs& a, const TileShape& t) {
 // at the measured step times, plus launch and epilogue.
 static float tile_time(const GemmArgs& a, const TileShape& t, int cus) {
   const int n = tile_count(a, t), full = n / (t.occ * cus), rem = n % (t.occ * cus);
-  const float steps = full * t.all + (rem == 0 ? 0.f : (rem > cus ? t.all : t.one));
+  float all = t.all;
+  // 6-block tiles, two to a weight tile, on part of the CUs twice: 1.21 to 1.29
+  // times that at widths 2560-5120 (7B gate/up at 164 rows: 73.5 us, 12 x 10 tiles 63)
+  if (t.tblk == 6 && full == 0 && a.mblocks <= 12) all *= 1.25f;
+  const float steps = full * all + (rem == 0 ? 0.f : (rem > cus ? all : t.one));
   return a.KB * steps + 10000.f + 4000.f * (full + (rem > 0) - 1);
 }
 
-static hipError_t device_cus(int& cus) {
+hipError_t device_cus(int& cus) {
   static std::atomic<int> known{0};
   cus = known.load(std::memory_order_relaxed);
   if (cus > 0) return hipSuccess;
@@ -364,6 +367,12 @@ static int best_tile(const GemmArgs& a, int n_shapes, int cus) {
   return best;
 }
 
+// Sliced launch, in us.  (Launches of the residual projections took 0.85 to 1.05
+// of tile_time, 0.93 at the median of 800.)
+static float gemm_tile_time(const GemmArgs& a, int cus) {
+  return 0.93e-3f * tile_time(a, kTiles[best_tile(a, kSlicedTiles, cus)], cus);
+}
+
 hipError_t launch_gemm_tile(const GemmArgs& a, int epi, hipStream_t s) {
   if (a.map == MAP_SINGLE || a.map == MAP_QKV_SINGLE || a.e.ssq_in) return hipErrorInvalidValue;
   int cus = 0;
@@ -383,14 +392,36 @@ hipError_t launch_gemm_tile(const GemmArgs& a, int epi, hipStream_t s) {
   }
 }
 
-// Whether a split-k session's launch goes to the tile kernel.  Above 160 rows
-// a split-k launch takes several token tiles that each stream the weights, so
-// always there, except the down projection up to 288 rows, whose one 18-block
-// tile per k slice is ahead (282 rows: 46 us against 80; its 344 k steps are
-// a long walk for one workgroup).  Up to 160 rows split-k is level or ahead
-// (7B gate/up at 148 rows: 48 us in a prompt pass against 52; QKV 40 and 40).
-bool tile_gemm_wanted(const GemmArgs& a, int epi) {
-  return a.mblocks > (epi == EPI_RESID && a.KB > kTileLongK ? 18 : 10);
+// The kernel of a split-k session's launch.  Up to 10 token blocks a split-k
+// launch is one token tile and level or ahead (7B gate/up at 148 rows 48 us in a
+// prompt pass, tile kernel 52; QKV 40 and 40).  Above, QKV and gate/up launches
+// fill the chip with whole tiles: split-k was behind at every width of 512-5120
+// and 161-1000 rows (width 512: 18 us, tile kernel 13; 4096 at 176 rows 67, 47).
+// A residual projection has a third or less of their tiles, and a workgroup of
+// the tile kernel walks its whole k range, so it takes the kernel expected to be
+// first, which at 190 of these widths and heights was never more than 1.6 us
+// behind the best.  Prompt pass per layer in us with the output projection on
+// tile / per-pair / tall split-k: width 1024 at 176 rows 84.3 / 78.8 / 86.0,
+// 2048 at 320 145 / 138, at 752 190 / 202; 4096 at 208 255 / 253 / 247, at 350
+// 291 / 303.  With the down projection on tile / split-k / tall split-k: 1536 (k
+// 6144) at 176 122 / 97 / 100, at 900 194 / 203; 2048 (5504) at 320 145 / 127, at
+// 752 190 / 208; 4096 (11008) at 276 259 / 240 / 226, at 350 291 / 298.
+GemmRoute gemm_route(GemmArgs& a, int epi, bool pairs, int NT, int cus) {
+  if (a.mblocks <= 10) return pairs ? GemmRoute::kPairs : GemmRoute::kSplit;
+  if (epi != EPI_RESID) return GemmRoute::kTile;
+  GemmRoute best = GemmRoute::kTile;
+  float t = gemm_tile_time(a, cus);
+  if (pairs) {
+    const float tp = gemm_ks_time(a, NT, cus);
+    if (tp < t) { t = tp; best = GemmRoute::kPairs; }
+  }
+  // (the per-pair kernel's k shares on split-k: in tall tiles of 8 slices only, as measured)
+  for (int tall = pairs ? 1 : 0; tall < 2; ++tall) {
+    if (tall && (!gemm_sk_tall_rows(a.M) || (pairs && a.splits != 8))) continue;
+    const float ts = gemm_sk_narrow_time(a, tall, cus);
+    if (ts < t) { t = ts; best = GemmRoute::kSplit; a.sk_tall = tall; }
+  }
+  return best;
 }
 
 }  // namespace gvc

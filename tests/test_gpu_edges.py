@@ -426,21 +426,22 @@ def test_many_row_tile_height_does_not_change_a_row():
 @pytest.mark.parametrize("views,text,batch", [(2, 33, 1), (4, 8, 1), (4, 32, 1), (2, 8, 2)],
                          ids=["161-rows", "264-rows", "288-rows", "2x136-rows"])
 def test_tall_split_k_tiles_agree_bit_for_bit(views, text, batch, monkeypatch):
-    """At 161-288 rows the split-k projections run one tile of 18 token
-    blocks per k slice instead of two tiles of 10, and the output projection
-    runs on the split-k core in 8 k slices instead of the per-pair kernel's
-    8 k shares (GVC_SK_TALL=0 turns both off).  Each slice's partial sums are
-    the same MFMA sequence either way and are added in the same order, so a
-    full step and a partial step give the same state bit for bit.  MID
-    with 161, 264 and 288 prompt rows: 11, 17 and 18 token blocks, the
-    lowest and highest heights that take a tall tile; and two episodes of
+    """At 161-288 rows split-k of the output and down projections can run one
+    tile of 18 token blocks per k slice (GVC_SK_TALL=2: both always do) instead
+    of two tiles of 10 and the per-pair kernel's 8 k shares (GVC_SK_TALL=0), or
+    the launch goes where it is expected to be fastest (the default, which at
+    these sizes takes the tile kernel, the per-pair kernel and tall tiles).  Each
+    slice's partial sums are the same MFMA sequence in all of them and are added
+    in the same order, so a full step and a partial step give the same state bit
+    for bit.  MID with 161, 264 and 288 prompt rows: 11, 17 and 18 token blocks,
+    the lowest and highest heights that take a tall tile; and two episodes of
     136 rows in one launch."""
     cfg = synth.config_mid().with_(n_views=views, n_text=text, batch=batch)
     assert 160 < cfg.batch * cfg.prompt_len <= 288
     w = synth.model_weights(cfg)
     si = synth.step_inputs(cfg, 96)
     states = []
-    for tall in ("1", "0"):
+    for tall in ("2", "0", "1"):
         monkeypatch.setenv("GVC_SK_TALL", tall)
         s = _session(cfg, w)
         monkeypatch.delenv("GVC_SK_TALL")
@@ -452,9 +453,49 @@ def test_tall_split_k_tiles_agree_bit_for_bit(views, text, batch, monkeypatch):
         s.step_prefill(ft, ids, None, mask)
         states.append(_state(s, cfg))
         s.close()
-    a, b = states
-    for x, y in zip(a[0] + a[1] + a[2] + [a[3]], b[0] + b[1] + b[2] + [b[3]]):
-        assert np.array_equal(x, y)
+    a = states[0]
+    for b in states[1:]:
+        for x, y in zip(a[0] + a[1] + a[2] + [a[3]], b[0] + b[1] + b[2] + [b[3]]):
+            assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("d,ffn,views,text", [(1536, 6144, 4, 32), (2048, 5504, 4, 64), (2048, 5504, 12, 10),
+                                              (4096, 512, 4, 8)],
+                         ids=["1536-288-rows", "2048-320-rows", "2048-778-rows", "4096-264-rows"])
+def test_residual_projections_take_a_fast_kernel(d, ffn, views, text, monkeypatch):
+    """Above 160 rows the output and down projections of a prompt pass take the
+    kernel that is expected to be fastest.  It is no more than 1.25 times as
+    slow as the tile kernel (GVC_SK_CORE=0) or as split-k and the per-pair
+    kernel (GVC_SK_TALL=0), by the smallest of six measurements in turn.  Of
+    these two the slower took 1.25 to 2 times as long as the other at all of these
+    sizes but one (output projection 4096 wide: 37 and 35 us)."""
+    from paper_2608_10824_amd import gvc
+    cfg = synth.config_mid().with_(d_model=d, n_heads=d // 128, ffn=ffn, n_views=views, n_text=text, n_layers=4)
+    w = synth.model_weights(cfg, device=DEV)
+    si = synth.step_inputs(cfg, 96)
+    fp, ids = si["frame_prev"].to(DEV), si["text_ids"].to(DEV)
+    runs = []
+    for env in ({}, {"GVC_SK_CORE": "0"}, {"GVC_SK_TALL": "0"}):
+        for k, v in env.items():
+            monkeypatch.setenv(k, v)
+        runs.append(_session(cfg, w))
+        for k in env:
+            monkeypatch.delenv(k)
+    best = [[1e9, 1e9] for _ in runs]
+    for _ in range(6):
+        for r, s in enumerate(runs):
+            for i, cls in enumerate((gvc.K_PREFILL_O, gvc.K_PREFILL_DOWN)):
+                gvc.profile_begin(s.ctx, cls, 4 * 3)
+                for _ in range(3):
+                    s.step_prefill(fp, ids)
+                ms, n = gvc.profile_end(s.ctx)
+                best[r][i] = min(best[r][i], ms * 1e3 / n)
+    for s in runs:
+        s.close()
+    print("us (output, down): default %s, tile kernel %s, split-k and per-pair %s" %
+          tuple(["%.1f %.1f" % tuple(b) for b in best]))
+    for i in range(2):
+        assert best[0][i] <= 1.25 * min(best[1][i], best[2][i])
 
 
 def test_split_k_cores_agree_bit_for_bit(monkeypatch):
