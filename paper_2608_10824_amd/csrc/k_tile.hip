@@ -34,7 +34,8 @@ namespace gvc {
 // numbers, then what they point to (RoPE, residual), then stores; one after
 // the other that chain cost a 7B QKV launch of 2368 rows 20 us per round of
 // tiles.  For QKV and the residual the row numbers of all blocks are loaded
-// first, and a block's operands while the block before it is stored.
+// first, and a block's operands while the block before it is stored (with
+// RoPE, without biases and the folded norm: launch_gemm_tile sees to it).
 template <int EPI, int WP, int TB>
 __device__ __forceinline__ void tile_epilogue(const GemmArgs& a, int pair0, int lane, int tb0,
                                               const floatx4 (&v)[2 * WP][TB]) {
@@ -42,109 +43,103 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& a, int pair0, int 
   const int col = lane & 15, sub = (lane >> 4) * 4;
   auto row = [&](int j) { return (tb0 + j) * 16 + col; };
   if constexpr (EPI == EPI_QKV) {
-    if (!e.bias[0] && e.rope) {
-      const int dh = e.head_dim, half = dh >> 1;
-      int pos[TB], ep[TB];
+    const int dh = e.head_dim, half = dh >> 1;
+    int pos[TB], ep[TB];
 #pragma unroll
-      for (int j = 0; j < TB; ++j) {
-        const int m = min(row(j), a.M - 1);
-        pos[j] = e.rows.pos[m];
-        ep[j] = e.rows.ep[m];
-      }
-      int mat[WP], head[WP], ia[WP];
+    for (int j = 0; j < TB; ++j) {
+      const int m = min(row(j), a.M - 1);
+      pos[j] = e.rows.pos[m];
+      ep[j] = e.rows.ep[m];
+    }
+    int mat[WP], head[WP], ia[WP];
+#pragma unroll
+    for (int p = 0; p < WP; ++p) {
+      int mb, bb, ba; bool ok;
+      map_pair(a, min(pair0 + p, a.n_pairs - 1), mat[p], ba, mb, bb, ok);
+      head[p] = ba / (dh >> 4);
+      ia[p] = (ba % (dh >> 4)) * 16 + sub;   // dim within head, < half
+    }
+    float4 cs[2][WP][2];   // (cos, sin) of 4 dims
+    auto load = [&](int j) __attribute__((always_inline)) {
 #pragma unroll
       for (int p = 0; p < WP; ++p) {
-        int mb, bb, ba; bool ok;
-        map_pair(a, min(pair0 + p, a.n_pairs - 1), mat[p], ba, mb, bb, ok);
-        head[p] = ba / (dh >> 4);
-        ia[p] = (ba % (dh >> 4)) * 16 + sub;   // dim within head, < half
+        const float4* r = (const float4*)(e.rope + (size_t)pos[j] * half + ia[p]);
+        cs[j & 1][p][0] = r[0];
+        cs[j & 1][p][1] = r[1];
       }
-      float4 cs[2][WP][2];   // (cos, sin) of 4 dims
-      auto load = [&](int j) __attribute__((always_inline)) {
+    };
+    load(0);
 #pragma unroll
-        for (int p = 0; p < WP; ++p) {
-          const float4* r = (const float4*)(e.rope + (size_t)pos[j] * half + ia[p]);
-          cs[j & 1][p][0] = r[0];
-          cs[j & 1][p][1] = r[1];
-        }
-      };
-      load(0);
+    for (int j = 0; j < TB; ++j) {
+      if (j + 1 < TB) load(j + 1);
+      const int m = row(j);
 #pragma unroll
-      for (int j = 0; j < TB; ++j) {
-        if (j + 1 < TB) load(j + 1);
-        const int m = row(j);
+      for (int p = 0; p < WP; ++p) {
+        if (pair0 + p >= a.n_pairs || m >= a.M) continue;
+        const floatx4 va = v[2 * p][j], vb = v[2 * p + 1][j];
+        if (mat[p] < 2) {
+          const float4 c0 = cs[j & 1][p][0], c1 = cs[j & 1][p][1];
+          const float c[4] = {c0.x, c0.z, c1.x, c1.z}, s[4] = {c0.y, c0.w, c1.y, c1.w};
+          u16x4 oa, ob;
 #pragma unroll
-        for (int p = 0; p < WP; ++p) {
-          if (pair0 + p >= a.n_pairs || m >= a.M) continue;
-          const floatx4 va = v[2 * p][j], vb = v[2 * p + 1][j];
-          if (mat[p] < 2) {
-            const float4 c0 = cs[j & 1][p][0], c1 = cs[j & 1][p][1];
-            const float c[4] = {c0.x, c0.z, c1.x, c1.z}, s[4] = {c0.y, c0.w, c1.y, c1.w};
-            u16x4 oa, ob;
+          for (int i = 0; i < 4; ++i) {
+            oa[i] = f2bf(rope_lo(va[i], vb[i], c[i], s[i]));
+            ob[i] = f2bf(rope_hi(va[i], vb[i], c[i], s[i]));
+          }
+          bf16* o = mat[p] == 0 ? e.q + (size_t)m * e.d + head[p] * dh
+                                : e.kc + ((size_t)(ep[j] * e.n_heads + head[p]) * e.kv_pad + pos[j]) * dh;
+          *(u16x4*)(o + ia[p]) = oa;
+          *(u16x4*)(o + ia[p] + half) = ob;
+        } else {
+          bf16* o = e.vc + (size_t)(ep[j] * e.n_heads + head[p]) * dh * e.kv_pad + pos[j];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              oa[i] = f2bf(rope_lo(va[i], vb[i], c[i], s[i]));
-              ob[i] = f2bf(rope_hi(va[i], vb[i], c[i], s[i]));
-            }
-            bf16* o = mat[p] == 0 ? e.q + (size_t)m * e.d + head[p] * dh
-                                  : e.kc + ((size_t)(ep[j] * e.n_heads + head[p]) * e.kv_pad + pos[j]) * dh;
-            *(u16x4*)(o + ia[p]) = oa;
-            *(u16x4*)(o + ia[p] + half) = ob;
-          } else {
-            bf16* o = e.vc + (size_t)(ep[j] * e.n_heads + head[p]) * dh * e.kv_pad + pos[j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              o[(size_t)(ia[p] + i) * e.kv_pad] = f2bf(va[i]);
-              o[(size_t)(ia[p] + half + i) * e.kv_pad] = f2bf(vb[i]);
-            }
+          for (int i = 0; i < 4; ++i) {
+            o[(size_t)(ia[p] + i) * e.kv_pad] = f2bf(va[i]);
+            o[(size_t)(ia[p] + half + i) * e.kv_pad] = f2bf(vb[i]);
           }
         }
       }
-      return;
     }
-  }
-  if constexpr (EPI == EPI_RESID) {
-    if (!e.bias[0] && !e.xn && a.map == MAP_PLAIN) {
-      size_t ri[TB], oi[TB];
-#pragma unroll
-      for (int j = 0; j < TB; ++j) {
-        const int m = min(row(j), a.M - 1), x = e.resid_mapped || e.out_mapped ? e.rows.idx[m] : m;
-        ri[j] = (size_t)(e.resid_mapped ? x : m) * e.d;
-        oi[j] = (size_t)(e.out_mapped ? x : m) * e.d;
-      }
-      const int last = 16 * a.wblk[0] - 4;   // blocks past the matrix re-read its last features
-      float4 r[2][2 * WP];
-      auto load = [&](int j) __attribute__((always_inline)) {
-#pragma unroll
-        for (int q = 0; q < 2 * WP; ++q)
-          r[j & 1][q] = *(const float4*)(e.resid + ri[j] + min((2 * pair0 + q) * 16 + sub, last));
-      };
-      load(0);
-#pragma unroll
-      for (int j = 0; j < TB; ++j) {
-        if (j + 1 < TB) load(j + 1);
-        if (row(j) >= a.M) continue;
-#pragma unroll
-        for (int q = 0; q < 2 * WP; ++q) {
-          const float4 x = r[j & 1][q];
-          const floatx4& y = v[q][j];
-          if (2 * pair0 + q < a.wblk[0])
-            *(float4*)(e.out + oi[j] + (2 * pair0 + q) * 16 + sub) =
-                float4{x.x + y[0], x.y + y[1], x.z + y[2], x.w + y[3]};
-        }
-      }
-      return;
-    }
-  }
-#pragma unroll
-  for (int p = 0; p < WP; ++p) {
-    if (pair0 + p >= a.n_pairs) continue;
-    int ma, ba, mb, bb; bool b_ok;
-    map_pair(a, pair0 + p, ma, ba, mb, bb, b_ok);
+  } else if constexpr (EPI == EPI_RESID) {
+    size_t ri[TB], oi[TB];
 #pragma unroll
     for (int j = 0; j < TB; ++j) {
-      const int m = row(j);
-      epilogue<EPI>(a, pair0 + p, lane, min(m, a.M - 1), v[2 * p][j], v[2 * p + 1][j], b_ok, m < a.M, 1.0f);
+      const int m = min(row(j), a.M - 1), x = e.resid_mapped || e.out_mapped ? e.rows.idx[m] : m;
+      ri[j] = (size_t)(e.resid_mapped ? x : m) * e.d;
+      oi[j] = (size_t)(e.out_mapped ? x : m) * e.d;
+    }
+    const int last = 16 * a.wblk[0] - 4;   // blocks past the matrix re-read its last features
+    float4 r[2][2 * WP];
+    auto load = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+      for (int q = 0; q < 2 * WP; ++q)
+        r[j & 1][q] = *(const float4*)(e.resid + ri[j] + min((2 * pair0 + q) * 16 + sub, last));
+    };
+    load(0);
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+      if (j + 1 < TB) load(j + 1);
+      if (row(j) >= a.M) continue;
+#pragma unroll
+      for (int q = 0; q < 2 * WP; ++q) {
+        const float4 x = r[j & 1][q];
+        const floatx4& y = v[q][j];
+        if (2 * pair0 + q < a.wblk[0])
+          *(float4*)(e.out + oi[j] + (2 * pair0 + q) * 16 + sub) =
+              float4{x.x + y[0], x.y + y[1], x.z + y[2], x.w + y[3]};
+      }
+    }
+  } else {
+#pragma unroll
+    for (int p = 0; p < WP; ++p) {
+      if (pair0 + p >= a.n_pairs) continue;
+      int ma, ba, mb, bb; bool b_ok;
+      map_pair(a, pair0 + p, ma, ba, mb, bb, b_ok);
+#pragma unroll
+      for (int j = 0; j < TB; ++j) {
+        const int m = row(j);
+        epilogue<EPI>(a, pair0 + p, lane, min(m, a.M - 1), v[2 * p][j], v[2 * p + 1][j], b_ok, m < a.M, 1.0f);
+      }
     }
   }
 }
@@ -375,6 +370,8 @@ static float gemm_tile_time(const GemmArgs& a, int cus) {
 
 hipError_t launch_gemm_tile(const GemmArgs& a, int epi, hipStream_t s) {
   if (a.map == MAP_SINGLE || a.map == MAP_QKV_SINGLE || a.e.ssq_in) return hipErrorInvalidValue;
+  if (epi == EPI_QKV && (a.e.bias[0] || a.e.bias[1] || a.e.bias[2] || !a.e.rope)) return hipErrorInvalidValue;
+  if (epi == EPI_RESID && (a.e.bias[0] || a.e.xn || a.map != MAP_PLAIN)) return hipErrorInvalidValue;
   int cus = 0;
   const hipError_t e = device_cus(cus);
   if (e != hipSuccess) return e;
