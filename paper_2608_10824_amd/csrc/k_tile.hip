@@ -7,16 +7,21 @@
 // operands' fragments of the tile are copied straight into LDS
 // (global_load_lds), S stages deep; wave (ww, wt) holds the fragments of step
 // k in registers and multiplies them while those of step k + 1 are read from
-// LDS, the reads spread between the MFMAs.  What bounds it is LDS: a wave tile
-// of 2 WP x TB blocks reads 2 WP + TB fragments per 2 WP * TB MFMAs, so
-// with the reads in front of the MFMAs (one register set, the kernel before
-// this one) the two took turns.  7B projections alone, reads in front -> beside
-// (best shape each): 2368 rows QKV 287 -> 234 us, output 94 -> 79, down 242 ->
-// 191; 736 rows 98 -> 77, 45 -> 35, gate/up 148 -> 135, down 143 -> 87.
+// LDS, the reads spread between the MFMAs.  A wave tile of 2 WP x TB blocks
+// reads 2 WP + TB fragments per 2 WP * TB MFMAs, and with the reads in front of
+// the MFMAs (one register set, the kernel before this one) LDS and the matrix
+// cores took turns.  7B projections alone, reads in front -> beside (best shape
+// each): 2368 rows QKV 287 -> 234 us, output 94 -> 79, down 242 -> 191; 736 rows
+// 98 -> 77, 45 -> 35, gate/up 148 -> 135, down 143 -> 87.  What bounds it now:
+// at 2368 rows the matrix cores are busy 41-57% of the cycles and LDS reads 19-24%
+// (no bank conflicts), while the tiles draw 9-11 TB/s from the L2s (gate/up 3.7 GB
+// in 380 us, down 2.2 GB in 197); at 276 rows 24-36% and 17-25%, and the same 10
+// TB/s.
 // Against split-k with fp32 partial sums and a kernel that adds them: 589 rows
 // QKV 147 -> 72 us, output 76 -> 32, gate/up 214 -> 123, down 121 -> 82; 282
-// rows QKV 56 -> 47, output 34 -> 29, gate/up 89 -> 60.  Ten shapes, because
-// whole rounds of workgroups on 256 CUs leave a rest that depends on the sizes.
+// rows QKV 56 -> 47, gate/up 89 -> 60 (launches alone; gemm_route has passes).
+// Ten shapes, because whole rounds of workgroups on 256 CUs leave a rest that
+// depends on the sizes.
 //
 // A row's sum runs over k in order, so it does not depend on the tile.  With
 // SL the sum is cut into the split-k launches' slices: a slice is summed from
