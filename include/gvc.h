@@ -272,8 +272,8 @@ int32_t gvc_step_prefill(gvc_ctx* ctx, const uint8_t* frame_t, const int32_t* te
  * before its embedding row is read).  The margins are also kept in the state for
  * gvc_margin_gate.  One episode's passes run in one launch (up to 256 layers of
  * passes per launch) that holds every compute unit until it ends (7B, 7 tokens:
- * 16 ms); kernels of other streams wait that long.  Errors: GVC_ESTATE if no prompt pass ran since the last
- * decode, GVC_EINVAL, GVC_EDEVICE. */
+ * 16 ms); kernels of other streams wait that long.  Errors: GVC_ESTATE if no
+ * prompt pass ran since the last decode, GVC_EINVAL, GVC_EDEVICE. */
 int32_t gvc_decode_actions(gvc_ctx* ctx, int32_t* tokens_out, float* margins_out,
                            float* logits_out, const int32_t* forced_tokens);
 
